@@ -167,14 +167,17 @@ int mlp_backward_dx(const mlp_t* h, const void* packed, const uint16_t* X,
  * Kernels: at widths 16, 32 and 64 with 2 to 5 weight matrices, one kernel
  * for the whole step (forward, loss, backward and weight gradients, the
  * hidden activations kept on chip: only X, T and Y touch memory).  Otherwise
- * the forward pass, then for nets of 2 to 5 weight matrices (at width 128
- * only ReLU nets with out_dim <= 16) one fused kernel that propagates the
- * deltas and accumulates the weight gradients without storing the deltas
- * (the fusion section V of the paper proposes), for other nets a backward
- * kernel and a weight-gradient kernel.  Then a fixed-order reduction, so G
- * and the loss are bitwise the same from run to run.  mlp_backward uses
- * the same rule for its backward kernels; mlp_backward_dx always the
- * unfused pair.
+ * the forward pass, then for ReLU nets of width 128 with 2 to 5 weight
+ * matrices and out_dim <= 16 one fused kernel that propagates the deltas and
+ * accumulates the weight gradients without storing the deltas (the fusion
+ * section V of the paper proposes); for other nets of widths 64 and 128 the
+ * same fusion in segments of a few layers, one kernel each, with only the
+ * delta between two segments stored; for other nets of widths 16 and 32 a
+ * backward kernel and a weight-gradient kernel.  Then a fixed-order
+ * reduction, so G and the loss are bitwise the same from run to run.
+ * mlp_backward fuses the 2 to 5 matrix nets of every width (at width 128
+ * under the same rule) and otherwise, as mlp_backward_dx does for every net
+ * of widths 64 and 128, runs the segments.
  */
 int mlp_train_step(const mlp_t* h, const void* packed, const uint16_t* X,
                    const float* T, uint16_t* Y, float* G, float* loss,

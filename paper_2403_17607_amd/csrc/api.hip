@@ -180,6 +180,15 @@ BwdArgs bwd_args(const mlp* h, const void* packed, const WsLayout& w, uint8_t* w
   return b;
 }
 
+// Whether a backward pass of this net reads the ReLU mask words: the fused
+// backward at width 128 and the unfused kernels of widths 16 and 32; the
+// others take relu' from the stashed activations, which they read anyway.
+bool reads_masks(const mlp* h) {
+  if (h->act != MLP_ACT_RELU) return false;
+  if (h->width == 128) return backward_fused_supported(h->width, n_mats(h), h->act, h->in_dim, h->out_dim);
+  return h->width < 64;
+}
+
 // Fixed-order sum of P weight-gradient partials (and the loss partials).
 int run_reduce(const mlp* h, const WsLayout& w, uint8_t* ws, int64_t M, int P, float* G,
                float* loss, int nloss, hipStream_t s) {
@@ -231,6 +240,54 @@ int run_fused_backward(const mlp* h, const void* packed, const uint16_t* X, cons
   if (e == hipErrorNotSupported) return 1;
   if (e != hipSuccess) return hip_fail(e, "fused backward kernel launch");
   return run_reduce(h, w, ws, M, P, G, loss, nloss, s);
+}
+
+// The segmented backward pass of a net of any depth (widths 64 and 128),
+// seeded from dY or from the output delta the training forward wrote, with
+// the input gradient when dX is given; then the reduce.
+int run_bwds(const mlp* h, const void* packed, const uint16_t* X, const float* dY, float* dX, const WsLayout& w,
+             uint8_t* ws, int64_t M, float* G, float* loss, int nloss, hipStream_t s) {
+  if (M <= 0) return run_reduce(h, w, ws, M, 0, G, loss, nloss, s);
+  const PackGeom g = pack_geom(h);
+  const int L = n_mats(h);
+  BwdsPlan p{};
+  hipError_t e = bwds_plan(h->width, L, h->act, M, &p);
+  if (e != hipSuccess) return hip_fail(e, "backward plan");
+  BwdsArgs b{};
+  const uint8_t* pk = static_cast<const uint8_t*>(packed);
+  b.packed = reinterpret_cast<const u32x4*>(pk + (size_t)g.fwd_total * 1024);
+  b.packed0 = reinterpret_cast<const u32x4*>(pk + (size_t)(g.fwd_total + g.bwd_total) * 1024);
+  b.X = X;
+  b.stashA = reinterpret_cast<const uint16_t*>(ws + w.stashA);
+  b.stashS = h->act == MLP_ACT_SINE ? reinterpret_cast<const uint16_t*>(ws + w.stashS) : nullptr;
+  b.cOut = h->out_act != MLP_ACT_LINEAR ? reinterpret_cast<const float*>(ws + w.cOut) : nullptr;
+  b.partial = reinterpret_cast<float*>(ws + w.partial);
+  b.M = M;
+  b.M16 = w.M16;
+  b.params = param_count(h);
+  b.in_dim = h->in_dim;
+  b.out_dim = h->out_dim;
+  b.act = h->act;
+  b.out_act = h->out_act;
+  b.L = L;
+  b.ntiles = p.ntiles;
+  b.grid = p.grid;
+  // D_l (l >= 1) in the workspace's hidden deltas, in the layer order of the stash
+  uint16_t* dh = reinterpret_cast<uint16_t*>(ws + w.deltaH);
+  auto delta = [&](int l) { return dh + (size_t)(l - 1) * w.M16 * h->width; };
+  int hi = L - 1;
+  for (int k = 0; k < p.nseg; ++k) {
+    b.hi = hi;
+    b.lo = hi - (p.base + (k < p.rem ? 1 : 0)) + 1;
+    b.deltaIn = k == 0 ? reinterpret_cast<const uint16_t*>(ws + w.deltaOut) : delta(hi + 1);
+    b.dY = k == 0 ? dY : nullptr;
+    b.deltaNext = b.lo > 0 ? delta(b.lo) : nullptr;
+    b.dX = b.lo == 0 ? dX : nullptr;
+    e = launch_bwds(h->width, b, s);
+    if (e != hipSuccess) return hip_fail(e, "segmented backward kernel launch");
+    hi = b.lo - 1;
+  }
+  return run_reduce(h, w, ws, M, p.grid, G, loss, nloss, s);
 }
 
 int run_wgrad_reduce(const mlp* h, const uint16_t* X, const WsLayout& w, uint8_t* ws, int64_t M,
@@ -517,7 +574,7 @@ int mlp_forward(const mlp_t* h, const void* packed, const uint16_t* X, uint16_t*
     uint8_t* ws = static_cast<uint8_t*>(stash);
     a.stashA = reinterpret_cast<uint16_t*>(ws + w.stashA);
     a.stashS = h->act == MLP_ACT_SINE ? reinterpret_cast<uint16_t*>(ws + w.stashS) : nullptr;
-    a.reluMask = h->act == MLP_ACT_RELU ? reinterpret_cast<uint32_t*>(ws + w.reluMask) : nullptr;
+    a.reluMask = reads_masks(h) ? reinterpret_cast<uint32_t*>(ws + w.reluMask) : nullptr;
     a.cOut = h->out_act != MLP_ACT_LINEAR ? reinterpret_cast<float*>(ws + w.cOut) : nullptr;
     mode = FWD_STASH;
   }
@@ -546,9 +603,10 @@ int mlp_backward_dx(const mlp_t* h, const void* packed, const uint16_t* X, const
   const WsLayout w = ws_layout(h, M);
   uint8_t* ws = static_cast<uint8_t*>(ws_);
   if (!dX && n_mats(h) > 1) {
-    const int rc = run_fused_backward(h, packed, X, dY, w, ws, M, G, nullptr, 0, 1, true, s);
+    const int rc = run_fused_backward(h, packed, X, dY, w, ws, M, G, nullptr, 0, 1, reads_masks(h), s);
     if (rc <= 0) return rc;
   }
+  if (h->width >= 64) return run_bwds(h, packed, X, dY, dX, w, ws, M, G, nullptr, 0, s);
   if (M > 0) {
     BwdArgs b = bwd_args(h, packed, w, ws, M);
     b.dY = dY;
@@ -636,7 +694,7 @@ int train_step_impl(const mlp_t* h, const void* packed, const uint16_t* X, const
     // training forward writes no mask words for it.
     const bool fused = n_mats(h) > 1 &&
                        backward_fused_supported(h->width, n_mats(h), h->act, h->in_dim, h->out_dim);
-    const bool masks = h->act == MLP_ACT_RELU && !(fused && h->width <= 64);
+    const bool masks = reads_masks(h) && !(fused && h->width <= 64);
     a.reluMask = masks ? reinterpret_cast<uint32_t*>(ws + w.reluMask) : nullptr;
     // At width 128 the fused backward takes the activations transposed
     // (the forward has matrix-core time to spare, the backward does not).
@@ -651,6 +709,7 @@ int train_step_impl(const mlp_t* h, const void* packed, const uint16_t* X, const
       if (rc <= 0) return rc;
       if (stash_t)  // no other backward reads the transposed stash
         return fail(MLP_ERR_UNSUPPORTED, "fused backward kernel unavailable on this device");
+      if (h->width >= 64) return run_bwds(h, packed, X, nullptr, nullptr, w, ws, M, G, loss, nloss, s);
       if (h->act == MLP_ACT_RELU && !masks)  // the unfused backward needs the masks
         return fail(MLP_ERR_UNSUPPORTED, "fused backward kernel unavailable on this device");
       BwdArgs b = bwd_args(h, packed, w, ws, M);
@@ -658,6 +717,7 @@ int train_step_impl(const mlp_t* h, const void* packed, const uint16_t* X, const
       if (e != hipSuccess) return hip_fail(e, "backward kernel launch");
     }
   }
+  if (h->width >= 64) return run_bwds(h, packed, X, nullptr, nullptr, w, ws, M, G, loss, nloss, s);
   return run_wgrad_reduce(h, X, w, ws, M, G, loss, nloss, s);
 }
 

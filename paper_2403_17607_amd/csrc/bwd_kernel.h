@@ -335,7 +335,7 @@ static hipError_t by_act(int act, int seeded, const BwdArgs& a, hipStream_t s) {
 }
 
 // Per-width entry points, each compiled in its own translation unit
-// (bwd16.hip .. bwd128.hip); bwd.hip dispatches on the width.
+// (bwd16.hip, bwd32.hip); bwd.hip dispatches on the width.
 template <int W>
 hipError_t launch_backward_w(int act, int seeded, const BwdArgs& a, hipStream_t s);
 

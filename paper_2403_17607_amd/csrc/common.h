@@ -177,6 +177,34 @@ struct TrainfArgs {
   uint32_t fwd_total;    // 1 KiB fragments of the forward-packed layers
 };
 
+// Segmented backward pass with the weight gradients (bwds_kernel): layers
+// hi .. lo of a net of any depth in one kernel; the delta entering the
+// segment is read once and the one leaving it written once, the deltas in
+// between stay on chip.
+constexpr int kBwdsWaves = 8;
+struct BwdsArgs {
+  const u32x4* packed;       // backward-packed weights, layers 1 .. L-1
+  const u32x4* packed0;      // backward-packed layer 0 (input gradient)
+  const uint16_t* X;         // [M][in_dim]
+  const uint16_t* stashA;    // (L-1) x [M16][W] tile images: a_1 .. a_{L-1}
+  const uint16_t* stashS;    // (L-1) x [M16][W] bf16 cos of sine layers, or null
+  const uint16_t* deltaIn;   // D_{hi+1}: [M16][W], or [M16][OP] of the output layer
+  const float* cOut;         // [M16][OP] fp32 pre-activation (seeded, nonlinear output)
+  const float* dY;           // [M][out_dim] (seeded), else null
+  uint16_t* deltaNext;       // D_lo: [M16][W] (lo > 0)
+  float* dX;                 // [M][in_dim] input gradient, or null (lo = 0)
+  float* partial;            // [gridDim.x][params]
+  int64_t M, M16, params;
+  int in_dim, out_dim, act, out_act;
+  int L, hi, lo;
+  int ntiles, grid;          // set by the launcher from bwds_plan
+};
+// The segments of a net: `nseg` of them, from the output down, the first
+// `rem` of base + 1 layers and the others of base.  grid workgroups each.
+struct BwdsPlan {
+  int nseg, base, rem, grid, ntiles;
+};
+
 struct WgradArgs {
   const uint16_t* X;
   const uint16_t* stashA;
@@ -242,6 +270,10 @@ hipError_t launch_train_fused(int width, int L, int act, int out_dim, const Trai
                               hipStream_t s, int* grid_out);
 // Whether launch_train_fused covers a net (host-side shape check only).
 bool train_fused_supported(int width, int L);
+// The segmented backward pass of one segment (a.hi .. a.lo), and the plan
+// of a whole net for M rows on the current device.
+hipError_t launch_bwds(int width, const BwdsArgs& a, hipStream_t s);
+hipError_t bwds_plan(int width, int L, int act, int64_t M, BwdsPlan* out);
 hipError_t launch_reduce(const ReduceArgs& a, hipStream_t s);
 hipError_t launch_pack(const PackArgs& a, hipStream_t s);
 hipError_t launch_optim(const OptArgs& a, hipStream_t s);

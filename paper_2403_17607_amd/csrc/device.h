@@ -176,6 +176,72 @@ __device__ __forceinline__ void bstore128(u32x4 v, rsrc_t r, uint32_t voff, uint
   __builtin_amdgcn_raw_buffer_store_b128(v, r, voff, soff, NT ? kStoreNT : 0);
 }
 
+// A_1 = X of NT 16-row blocks from row0 on, in input order: lane (g, i) of
+// block n gets features 32 kb + 8 g .. + 7 of row 16 n + i.  in_dim a
+// multiple of 8: aligned 16-byte buffer loads, 0 past the row and past M.
+// Other widths: rows start at any 2-byte address, so each lane's eight
+// features still come in one 16-byte load, unaligned, which reads on into
+// the next row; mask_x_rows, called when the values are first used (the
+// loads stay in flight until then), clears what is past in_dim.  Only where
+// such a load would pass the end of X are the features loaded one by one.
+typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
+template <int NT, int KBW>
+__device__ __forceinline__ void load_x_rows(const uint16_t* X, int64_t row0, int64_t M, int in_dim, int li, int lg,
+                                            u32x4 (&dst)[NT][KBW]) {
+  int64_t vr = M - row0;
+  vr = vr < 0 ? 0 : (vr > NT * 16 ? NT * 16 : vr);
+  const rsrc_t xr = make_rsrc(X + row0 * in_dim, vr * in_dim * 2);
+  if ((in_dim & 7) == 0) {
+#pragma unroll
+    for (int kb = 0; kb < KBW; ++kb) {
+      const int f0 = kb * 32 + lg * 8;
+      const uint32_t voff = f0 < in_dim ? (uint32_t)((li * in_dim + f0) * 2) : kOOB;
+#pragma unroll
+      for (int n = 0; n < NT; ++n) dst[n][kb] = bload128(xr, voff, (uint32_t)(n * 32 * in_dim));
+    }
+  } else if ((row0 + NT * 16) * in_dim + 8 <= M * in_dim) {
+    // the last element any lane reads is at most 7 past block NT - 1's end
+    const uint16_t* p = X + row0 * in_dim;
+#pragma unroll
+    for (int kb = 0; kb < KBW; ++kb) {
+      const int f0 = kb * 32 + lg * 8;
+      const uint32_t eo = (uint32_t)(li * in_dim + (f0 < in_dim ? f0 : 0));
+#pragma unroll
+      for (int n = 0; n < NT; ++n)
+        dst[n][kb] = *reinterpret_cast<const u32x4_a2*>(p + (uint32_t)(n * 16 * in_dim) + eo);
+    }
+  } else {
+#pragma unroll
+    for (int kb = 0; kb < KBW; ++kb) {
+      const int f0 = kb * 32 + lg * 8;
+#pragma unroll
+      for (int n = 0; n < NT; ++n) {
+        uint32_t e[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+          e[q] = bload16(xr, f0 + q < in_dim ? (uint32_t)((li * in_dim + f0 + q) * 2) : kOOB, (uint32_t)(n * 32 * in_dim));
+        dst[n][kb] = u32x4{e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
+        __builtin_amdgcn_sched_barrier(0);  // one piece at a time: bounds the registers
+      }
+    }
+  }
+}
+template <int NT, int KBW>
+__device__ __forceinline__ void mask_x_rows(int in_dim, int lg, u32x4 (&x)[NT][KBW]) {
+  if ((in_dim & 7) == 0) return;
+#pragma unroll
+  for (int kb = 0; kb < KBW; ++kb) {
+    if (32 * kb + 32 <= in_dim) continue;
+    const int v = in_dim - 32 * kb - 8 * lg;  // features of this lane's piece
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t m = v >= 2 * j + 2 ? 0xffffffffu : (v == 2 * j + 1 ? 0xffffu : 0u);
+#pragma unroll
+      for (int n = 0; n < NT; ++n) x[n][kb][j] &= m;
+    }
+  }
+}
+
 // Asynchronous copy of nfrag 1 KiB fragments from global memory into LDS
 // with direct-to-LDS loads (no registers): wave w copies fragments w,
 // w + nwaves, ...; lane l of a load writes bytes 16 l .. 16 l + 15 of the

@@ -389,8 +389,6 @@ hipError_t launch_wgrad(int width, const WgradArgs& a, hipStream_t s) {
   switch (width) {
     case 16: return wgrad_t<16>(a, s);
     case 32: return wgrad_t<32>(a, s);
-    case 64: return wgrad_t<64>(a, s);
-    case 128: return wgrad_t<128>(a, s);
     default: return hipErrorInvalidValue;
   }
 }

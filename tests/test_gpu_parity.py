@@ -277,6 +277,21 @@ def test_random_shapes_input_gradient(ffmlp, gpu, width, depth, in_dim, out_dim,
             seed=width + depth + in_dim + out_dim + M)
 
 
+@pytest.mark.parametrize("width,depth", [(64, 0), (64, 4), (64, 5), (64, 10), (128, 0), (128, 2), (128, 3), (128, 6)])
+@pytest.mark.parametrize("in_dim,out_dim,M,act,out_act", [(1, 2, 1, "relu", "sigmoid"),
+                                                          (63, 17, 257, "sigmoid", "linear"),
+                                                          (33, 64, 255, "sine", "relu"),
+                                                          (64, 3, 4001, "linear", "sine")])
+def test_segmented_backward(ffmlp, gpu, width, depth, in_dim, out_dim, M, act, out_act):
+    """The segmented backward (widths 64 and 128): one segment and several,
+    both segment lengths, each activation class, one row, a tile's edges, X
+    rows that no vector load fits (also where the last row's would pass the
+    end of X), output strips from one to all; seeded and from the training
+    forward, with and without dX."""
+    dx_case(ffmlp, gpu, width, depth, in_dim, out_dim, M, act, out_act, seed=31)
+    run_case(ffmlp, gpu, width, depth, in_dim, out_dim, M, act, out_act, seed=32)
+
+
 def test_input_gradient_streaming(ffmlp, gpu):
     """Weights too large for LDS (staged layer by layer) with dX."""
     dx_case(ffmlp, gpu, 128, 16, 128, 128, 3000)
