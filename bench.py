@@ -73,7 +73,9 @@ def train_bytes_per_row(width, depth, in_dim, out_dim, act, fused=None, masks=Tr
     activations (the weight-gradient operands; at widths up to 64 also the
     ReLU and sigmoid derivative source), plus the masks at width 128 and the
     cos stash of sine nets, and writes no deltas.
-    Three-kernel plan: the backward reads the output delta and the
+    Three-kernel plan (an unfused backward; the library runs the other nets
+    in fused segments, which move less, and their rate is quoted against
+    this count all the same): the backward reads the output delta and the
     derivative source of every hidden activation (ReLU: its mask, 16 B per
     row, or with masks=False the activation itself; sigmoid: the
     activation; sine: the stored cos; linear: nothing) and writes the hidden
@@ -399,11 +401,11 @@ def main():
                                        " (the whole step) + reduce_kernel"
                                        if fused_step(width, depth) else
                                        ("fwd_kernel (train) + " +
-                                        ("bwdn_kernel" if width <= 32 else "bwdg_kernel") +
-                                        " (fused backward and weight gradients) + reduce_kernel")
+                                        "bwdg_kernel (fused backward and weight gradients) + "
+                                        "reduce_kernel")
                                        if fused else
-                                       ("fwd_kernel (train) + bwd_kernel + wgrad_kernel + "
-                                        "reduce_kernel")),
+                                       ("fwd_kernel (train) + bwds_kernel (fused backward and "
+                                        "weight gradients, in segments) + reduce_kernel")),
                            "bound": "hbm", "achieved": train_gbs,
                            "peak": PEAK_HBM_GBS, "unit": "GB/s",
                            "frac": train_gbs / PEAK_HBM_GBS,

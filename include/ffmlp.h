@@ -170,14 +170,12 @@ int mlp_backward_dx(const mlp_t* h, const void* packed, const uint16_t* X,
  * the forward pass, then for ReLU nets of width 128 with 2 to 5 weight
  * matrices and out_dim <= 16 one fused kernel that propagates the deltas and
  * accumulates the weight gradients without storing the deltas (the fusion
- * section V of the paper proposes); for other nets of widths 64 and 128 the
- * same fusion in segments of a few layers, one kernel each, with only the
- * delta between two segments stored; for other nets of widths 16 and 32 a
- * backward kernel and a weight-gradient kernel.  Then a fixed-order
- * reduction, so G and the loss are bitwise the same from run to run.
- * mlp_backward fuses the 2 to 5 matrix nets of every width (at width 128
- * under the same rule) and otherwise, as mlp_backward_dx does for every net
- * of widths 64 and 128, runs the segments.
+ * section V of the paper proposes); for other nets the same fusion in
+ * segments of a few layers (up to 9, 7, 5 and 3 at widths 16, 32, 64 and
+ * 128), one kernel each, with only the delta between two segments stored.
+ * Then a fixed-order reduction, so G and the loss are bitwise the same from
+ * run to run.  mlp_backward runs the width-128 fused kernel under the same
+ * rule and otherwise, as mlp_backward_dx does for every net, the segments.
  */
 int mlp_train_step(const mlp_t* h, const void* packed, const uint16_t* X,
                    const float* T, uint16_t* Y, float* G, float* loss,

@@ -82,7 +82,6 @@ PackGeom pack_geom(const mlp* h) {
 struct WsLayout {
   int64_t M16;
   size_t stashA, stashS, reluMask, deltaH, deltaOut, cOut, partial, lossPart, total;
-  int P, chunks_per_block;
 };
 
 WsLayout ws_layout(const mlp* h, int64_t M) {
@@ -99,17 +98,17 @@ WsLayout ws_layout(const mlp* h, int64_t M) {
   w.deltaH = o; o = round_up(o + hid, 256);
   w.deltaOut = o; o = round_up(o + (size_t)w.M16 * OP * 2, 256);
   w.cOut = o; o = round_up(o + (h->out_act != MLP_ACT_LINEAR ? (size_t)w.M16 * OP * 4 : 0), 256);
-  const int CH = wgrad_chunk(W);
+  // Room for the partial sums of up to kPartialTarget / L workgroups of
+  // partial_rows rows or more each.
+  const int CH = partial_rows(W);
   const int64_t nch = (M + CH - 1) / CH;
-  int64_t P = (kWgradTargetBlocks + L - 1) / L;
+  int64_t P = (kPartialTarget + L - 1) / L;
   if (P > nch) P = nch;
   if (P < 1) P = 1;
   const int64_t cpb = nch > 0 ? (nch + P - 1) / P : 0;
-  P = cpb > 0 ? (nch + cpb - 1) / cpb : 1;  // no empty workgroups
-  w.P = (int)P;
-  w.chunks_per_block = (int)cpb;
-  // The fused backward writes one partial per workgroup, at most one per
-  // row tile and at most kBwdgMaxBlocks.
+  P = cpb > 0 ? (nch + cpb - 1) / cpb : 1;
+  // The backward and one-kernel training kernels write one partial per
+  // workgroup, at most one per 128 rows and at most kBwdgMaxBlocks.
   int64_t Pf = (M + kBwdgRows - 1) / kBwdgRows;
   if (Pf > kBwdgMaxBlocks) Pf = kBwdgMaxBlocks;
   const int64_t Pmax = P > Pf ? P : Pf;
@@ -154,39 +153,12 @@ FwdArgs fwd_args(const mlp* h, const void* packed, const uint16_t* X, int64_t M)
   return a;
 }
 
-BwdArgs bwd_args(const mlp* h, const void* packed, const WsLayout& w, uint8_t* ws, int64_t M) {
-  const PackGeom g = pack_geom(h);
-  BwdArgs b{};
-  b.packed = reinterpret_cast<const u32x4*>(static_cast<const uint8_t*>(packed) + (size_t)g.fwd_total * 1024);
-  b.stashA = reinterpret_cast<const uint16_t*>(ws + w.stashA);
-  b.stashS = h->act == MLP_ACT_SINE ? reinterpret_cast<const uint16_t*>(ws + w.stashS) : nullptr;
-  b.deltaH = reinterpret_cast<uint16_t*>(ws + w.deltaH);
-  b.deltaOut = reinterpret_cast<uint16_t*>(ws + w.deltaOut);
-  b.cOut = h->out_act != MLP_ACT_LINEAR ? reinterpret_cast<const float*>(ws + w.cOut) : nullptr;
-  b.reluMask = h->act == MLP_ACT_RELU ? reinterpret_cast<const uint32_t*>(ws + w.reluMask) : nullptr;
-  b.M = M;
-  b.M16 = w.M16;
-  b.in_dim = h->in_dim;
-  b.out_dim = h->out_dim;
-  b.L = n_mats(h);
-  b.out_act = h->out_act;
-  const int64_t rows = tile_rows(h->width);
-  b.ntiles = (int)((M + rows - 1) / rows);
-  b.layH_frags = g.bwd_hidden;
-  b.total_frags = g.bwd_total;
-  b.packed0 = reinterpret_cast<const u32x4*>(static_cast<const uint8_t*>(packed) +
-                                             (size_t)(g.fwd_total + g.bwd_total) * 1024);
-  b.dX = nullptr;
-  return b;
-}
-
-// Whether a backward pass of this net reads the ReLU mask words: the fused
-// backward at width 128 and the unfused kernels of widths 16 and 32; the
-// others take relu' from the stashed activations, which they read anyway.
+// Whether a backward pass of this net reads the ReLU mask words: only the
+// fused backward at width 128 (the others take relu' from the stashed
+// activations, which they read anyway).
 bool reads_masks(const mlp* h) {
-  if (h->act != MLP_ACT_RELU) return false;
-  if (h->width == 128) return backward_fused_supported(h->width, n_mats(h), h->act, h->in_dim, h->out_dim);
-  return h->width < 64;
+  return h->act == MLP_ACT_RELU &&
+         backward_fused_supported(h->width, n_mats(h), h->act, h->out_dim);
 }
 
 // Fixed-order sum of P weight-gradient partials (and the loss partials).
@@ -207,20 +179,16 @@ int run_reduce(const mlp* h, const WsLayout& w, uint8_t* ws, int64_t M, int P, f
 }
 
 // The fused backward pass with the weight gradients, then the reduce.
-// Returns 1 (nothing enqueued) when the fused kernel does not cover the net.
+// For nets that backward_fused_supported covers, M > 0.
 int run_fused_backward(const mlp* h, const void* packed, const uint16_t* X, const float* dY,
                        const WsLayout& w, uint8_t* ws, int64_t M, float* G, float* loss, int nloss,
-                       int seeded, bool masks, hipStream_t s, bool stash_t = false) {
-  if (M <= 0 || !backward_fused_supported(h->width, n_mats(h), h->act, h->in_dim, h->out_dim))
-    return 1;
+                       int seeded, bool stash_t, hipStream_t s) {
   const PackGeom g = pack_geom(h);
   BwdgArgs a{};
   a.packed = reinterpret_cast<const u32x4*>(static_cast<const uint8_t*>(packed) + (size_t)g.fwd_total * 1024);
   a.X = X;
   a.stashA = reinterpret_cast<const uint16_t*>(ws + w.stashA);
-  a.reluMask = (h->act == MLP_ACT_RELU && masks) ? reinterpret_cast<const uint32_t*>(ws + w.reluMask)
-                                                 : nullptr;
-  a.stashS = h->act == MLP_ACT_SINE ? reinterpret_cast<const uint16_t*>(ws + w.stashS) : nullptr;
+  a.reluMask = reinterpret_cast<const uint32_t*>(ws + w.reluMask);
   a.deltaOut = reinterpret_cast<const uint16_t*>(ws + w.deltaOut);
   a.cOut = h->out_act != MLP_ACT_LINEAR ? reinterpret_cast<const float*>(ws + w.cOut) : nullptr;
   a.dY = dY;
@@ -230,20 +198,17 @@ int run_fused_backward(const mlp* h, const void* packed, const uint16_t* X, cons
   a.params = param_count(h);
   a.in_dim = h->in_dim;
   a.out_dim = h->out_dim;
-  a.act = h->act;
   a.out_act = h->out_act;
   a.ntiles = (int)((M + kBwdgRows - 1) / kBwdgRows);
   a.layH_frags = g.bwd_hidden;
   a.stash_t = stash_t ? 1 : 0;
   int P = 0;
-  hipError_t e = launch_backward_fused(h->width, n_mats(h), h->out_dim, seeded, a, s, &P);
-  if (e == hipErrorNotSupported) return 1;
+  hipError_t e = launch_backward_fused(n_mats(h), seeded, a, s, &P);
   if (e != hipSuccess) return hip_fail(e, "fused backward kernel launch");
   return run_reduce(h, w, ws, M, P, G, loss, nloss, s);
 }
 
-// The segmented backward pass of a net of any depth (widths 64 and 128),
-// seeded from dY or from the output delta the training forward wrote, with
+// The segmented backward pass of a net of any depth, seeded from dY or from the output delta the training forward wrote, with
 // the input gradient when dX is given; then the reduce.
 int run_bwds(const mlp* h, const void* packed, const uint16_t* X, const float* dY, float* dX, const WsLayout& w,
              uint8_t* ws, int64_t M, float* G, float* loss, int nloss, hipStream_t s) {
@@ -288,30 +253,6 @@ int run_bwds(const mlp* h, const void* packed, const uint16_t* X, const float* d
     hi = b.lo - 1;
   }
   return run_reduce(h, w, ws, M, p.grid, G, loss, nloss, s);
-}
-
-int run_wgrad_reduce(const mlp* h, const uint16_t* X, const WsLayout& w, uint8_t* ws, int64_t M,
-                     float* G, float* loss, int nloss, hipStream_t s) {
-  const int64_t params = param_count(h);
-  if (M > 0) {
-    WgradArgs a{};
-    a.X = X;
-    a.stashA = reinterpret_cast<const uint16_t*>(ws + w.stashA);
-    a.deltaH = reinterpret_cast<const uint16_t*>(ws + w.deltaH);
-    a.deltaOut = reinterpret_cast<const uint16_t*>(ws + w.deltaOut);
-    a.partial = reinterpret_cast<float*>(ws + w.partial);
-    a.M = M;
-    a.M16 = w.M16;
-    a.params = params;
-    a.in_dim = h->in_dim;
-    a.out_dim = h->out_dim;
-    a.L = n_mats(h);
-    a.P = w.P;
-    a.chunks_per_block = w.chunks_per_block;
-    hipError_t e = launch_wgrad(h->width, a, s);
-    if (e != hipSuccess) return hip_fail(e, "weight-gradient kernel launch");
-  }
-  return run_reduce(h, w, ws, M, w.P, G, loss, nloss, s);
 }
 
 int train_step_impl(const mlp_t* h, const void* packed, const uint16_t* X, const float* T,
@@ -602,19 +543,8 @@ int mlp_backward_dx(const mlp_t* h, const void* packed, const uint16_t* X, const
   hipStream_t s = static_cast<hipStream_t>(stream);
   const WsLayout w = ws_layout(h, M);
   uint8_t* ws = static_cast<uint8_t*>(ws_);
-  if (!dX && n_mats(h) > 1) {
-    const int rc = run_fused_backward(h, packed, X, dY, w, ws, M, G, nullptr, 0, 1, reads_masks(h), s);
-    if (rc <= 0) return rc;
-  }
-  if (h->width >= 64) return run_bwds(h, packed, X, dY, dX, w, ws, M, G, nullptr, 0, s);
-  if (M > 0) {
-    BwdArgs b = bwd_args(h, packed, w, ws, M);
-    b.dY = dY;
-    b.dX = dX;
-    hipError_t e = launch_backward(h->width, h->act, 1, b, s);
-    if (e != hipSuccess) return hip_fail(e, "backward kernel launch");
-  }
-  return run_wgrad_reduce(h, X, w, ws, M, G, nullptr, 0, s);
+  if (!dX && M > 0 && reads_masks(h)) return run_fused_backward(h, packed, X, dY, w, ws, M, G, nullptr, 0, 1, false, s);
+  return run_bwds(h, packed, X, dY, dX, w, ws, M, G, nullptr, 0, s);
 }
 
 int mlp_train_step(const mlp_t* h, const void* packed, const uint16_t* X, const float* T,
@@ -661,7 +591,7 @@ int train_step_impl(const mlp_t* h, const void* packed, const uint16_t* X, const
   uint8_t* ws = static_cast<uint8_t*>(ws_);
   int nloss = 0;
   if (M > 0 && train_fused_supported(h->width, n_mats(h))) {
-    // Widths 16 and 32: the whole step in one kernel, then the reduce.
+    // The whole step in one kernel, then the reduce.
     const PackGeom g = pack_geom(h);
     TrainfArgs t{};
     t.packedF = static_cast<const u32x4*>(packed);
@@ -680,8 +610,8 @@ int train_step_impl(const mlp_t* h, const void* packed, const uint16_t* X, const
     t.fwd_total = g.fwd_total;
     int P = 0;
     hipError_t e = launch_train_fused(h->width, n_mats(h), h->act, h->out_dim, t, s, &P);
-    if (e == hipSuccess) return run_reduce(h, w, ws, M, P, G, loss, P, s);
-    if (e != hipErrorNotSupported) return hip_fail(e, "fused training kernel launch");
+    if (e != hipSuccess) return hip_fail(e, "fused training kernel launch");
+    return run_reduce(h, w, ws, M, P, G, loss, P, s);
   }
   if (M > 0) {
     FwdArgs a = fwd_args(h, packed, X, M);
@@ -689,36 +619,18 @@ int train_step_impl(const mlp_t* h, const void* packed, const uint16_t* X, const
     a.T = T;
     a.stashA = reinterpret_cast<uint16_t*>(ws + w.stashA);
     a.stashS = h->act == MLP_ACT_SINE ? reinterpret_cast<uint16_t*>(ws + w.stashS) : nullptr;
-    // The fused backward at widths up to 64 reads relu' from the stashed
-    // activations (which it reads for the weight gradients anyway), so the
-    // training forward writes no mask words for it.
-    const bool fused = n_mats(h) > 1 &&
-                       backward_fused_supported(h->width, n_mats(h), h->act, h->in_dim, h->out_dim);
-    const bool masks = reads_masks(h) && !(fused && h->width <= 64);
-    a.reluMask = masks ? reinterpret_cast<uint32_t*>(ws + w.reluMask) : nullptr;
-    // At width 128 the fused backward takes the activations transposed
-    // (the forward has matrix-core time to spare, the backward does not).
-    const bool stash_t = fused && h->width == 128 && masks;
-    a.stash_t = stash_t ? 1 : 0;
+    // The fused backward at width 128 takes the activations transposed (the
+    // forward has matrix-core time to spare, the backward does not).
+    const bool fused = reads_masks(h);
+    a.reluMask = fused ? reinterpret_cast<uint32_t*>(ws + w.reluMask) : nullptr;
+    a.stash_t = fused ? 1 : 0;
     a.deltaOut = reinterpret_cast<uint16_t*>(ws + w.deltaOut);
     a.lossPart = reinterpret_cast<float*>(ws + w.lossPart);
     hipError_t e = launch_forward(h->width, h->act, FWD_TRAIN, a, s, &nloss);
     if (e != hipSuccess) return hip_fail(e, "forward kernel launch");
-    if (n_mats(h) > 1) {
-      const int rc = run_fused_backward(h, packed, X, nullptr, w, ws, M, G, loss, nloss, 0, masks, s, stash_t);
-      if (rc <= 0) return rc;
-      if (stash_t)  // no other backward reads the transposed stash
-        return fail(MLP_ERR_UNSUPPORTED, "fused backward kernel unavailable on this device");
-      if (h->width >= 64) return run_bwds(h, packed, X, nullptr, nullptr, w, ws, M, G, loss, nloss, s);
-      if (h->act == MLP_ACT_RELU && !masks)  // the unfused backward needs the masks
-        return fail(MLP_ERR_UNSUPPORTED, "fused backward kernel unavailable on this device");
-      BwdArgs b = bwd_args(h, packed, w, ws, M);
-      e = launch_backward(h->width, h->act, 0, b, s);
-      if (e != hipSuccess) return hip_fail(e, "backward kernel launch");
-    }
+    if (fused) return run_fused_backward(h, packed, X, nullptr, w, ws, M, G, loss, nloss, 0, true, s);
   }
-  if (h->width >= 64) return run_bwds(h, packed, X, nullptr, nullptr, w, ws, M, G, loss, nloss, s);
-  return run_wgrad_reduce(h, X, w, ws, M, G, loss, nloss, s);
+  return run_bwds(h, packed, X, nullptr, nullptr, w, ws, M, G, loss, nloss, s);
 }
 
 }  // namespace

@@ -13,14 +13,13 @@
 //
 // A workgroup of eight waves owns tiles of 128 NT rows (persistent loop).
 // Each wave carries the deltas of its own 16 NT rows through the layers in
-// VGPRs (chain order, weights resident in LDS).  Per layer it writes its rows
-// of D_{l+1} and A_l, transposed on the matrix cores (MFMA against a 0/1
-// selection matrix, exact), into the LDS tiles DT and AT [feature][row];
-// after a barrier every wave accumulates its fixed slice of G_l from them,
-// interleaved with the delta product of its own rows, whose derivative
-// sigma'(A_l) comes from the same registers.  The activations of a layer
-// are requested a whole tile ahead (the layer's registers are free as soon
-// as its delta product is done), so the kernel streams the stash.
+// VGPRs (chain order, weights resident in LDS).  Per layer it stores its rows
+// of D_{l+1} and A_l as they are into the LDS row tiles DT and AT; after a
+// barrier every wave accumulates its fixed slice of G_l from them (transposing
+// LDS reads), interleaved with the delta product of its own rows, whose
+// derivative sigma'(A_l) comes from the same registers.  The activations of
+// the next two layers (of this tile or the next) are in flight while a layer
+// computes, so the kernel streams the stash.
 #pragma once
 
 #include "device.h"
@@ -29,33 +28,38 @@ namespace ffmlp {
 
 enum { BWDS_RELU = 0, BWDS_SINE = 1, BWDS_OTHER = 2 };
 
-// 16-row blocks per wave.
-template <int W> constexpr int bwds_nt() { return W == 64 ? 2 : 1; }
+// One 16-row block per wave.  At width 64 two fit, but with one the kernel
+// takes 128 registers and two workgroups share a CU: the same speed on large
+// batches (training step of 9 matrices, 683354 rows: 499 us both), and twice
+// the workgroups on small ones (17 matrices, 20000 rows: 109 -> 94 us).
+template <int W> constexpr int bwds_nt() { return 1; }
 
 template <int W, int NL>
 struct BwdsGeom {
   static constexpr int NW = kBwdsWaves, NT = bwds_nt<W>(), SW = W / 16, KBW = (W + 31) / 32;
-  static constexpr int ROWS = NW * NT * 16, LDT = ROWS, KS = ROWS / 32;
+  static constexpr int ROWS = NW * NT * 16, KS = ROWS / 32;
   static constexpr int LF = SW * KBW;  // 1 KiB fragments of one layer
   // G slices: TK x TJ tiles of 16x16 per wave and layer.
   static constexpr int TK = W == 128 ? 2 : 1, TJ = W == 128 ? 4 : 2;
   static constexpr int JG = SW / TJ;   // waves that share a k-strip group
   static constexpr int TPW = TK * TJ;
   static constexpr size_t tiles_off() { return (size_t)NL * LF * 1024; }
-  static constexpr size_t lds_bytes() { return tiles_off() + (size_t)2 * W * LDT * 2; }
+  static constexpr size_t lds_bytes() { return tiles_off() + (size_t)2 * ROWS * W * 2; }
   static_assert(W >= 64 && (SW / TK) * JG == NW, "slices cover G");
 };
 
 template <int W, int NL, bool TOP, bool BOT, bool SEEDED, int AC>
-__global__ __launch_bounds__(kBwdsWaves * 64) void bwds_kernel(const BwdsArgs a) {
+__global__ __launch_bounds__(kBwdsWaves * 64, (W == 64 ? 4 : 2)) void bwds_kernel(const BwdsArgs a) {
   using Gm = BwdsGeom<W, NL>;
-  constexpr int NW = Gm::NW, NT = Gm::NT, SW = Gm::SW, KBW = Gm::KBW, LDT = Gm::LDT, KS = Gm::KS;
+  constexpr int NW = Gm::NW, NT = Gm::NT, SW = Gm::SW, KBW = Gm::KBW, KS = Gm::KS;
   constexpr int LF = Gm::LF, TK = Gm::TK, TJ = Gm::TJ, TPW = Gm::TPW;
   static_assert(TOP || !SEEDED, "dY enters at the output layer");
-  constexpr bool XLATE = W == 128 && BOT && NL > 1;
+  constexpr int AHEAD = NL < 3 ? NL - 1 : 2;  // layers whose A is in flight while one computes
+  constexpr bool XLATE = BOT && NL > (W == 128 ? 1 : 3);
   extern __shared__ u32x4 smem[];
-  uint16_t* DT = reinterpret_cast<uint16_t*>(reinterpret_cast<uint8_t*>(smem) + Gm::tiles_off());
-  uint16_t* AT = DT + (size_t)W * LDT;
+  using RT = RowTile<W>;
+  uint8_t* DT = reinterpret_cast<uint8_t*>(smem) + Gm::tiles_off();
+  uint8_t* AT = DT + (size_t)Gm::ROWS * W * 2;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform
   const int li = lane & 15, lg = lane >> 4;
@@ -75,46 +79,17 @@ __global__ __launch_bounds__(kBwdsWaves * 64) void bwds_kernel(const BwdsArgs a)
       stage_frags(smem + (size_t)i * LF * 64, a.packed + (size_t)(hi - i - 1) * LF * 64, (uint32_t)LF, wave, NW, lane);
     }
   });
-  // Selection matrices: an MFMA of a chain-order operand (lane (g, i): row
-  // i, slots 0-3 features 4 g + q of one strip, slots 4-7 of the next)
-  // against sel0 (sel1) gives lane (g, n) feature n of the first (second)
-  // strip for rows 4 g .. 4 g + 3.
-  u32x4 sel0 = {0u, 0u, 0u, 0u}, sel1 = {0u, 0u, 0u, 0u};
-  {
-    const int q = li - 4 * lg;
-    if (q >= 0 && q < 4) {
-      const uint32_t one = 0x3F80u << (16 * (q & 1));
-      if (q < 2) {
-        sel0.x = one;
-        sel1.z = one;
-      } else {
-        sel0.y = one;
-        sel1.w = one;
-      }
-    }
-  }
   const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
   f32x4 gacc[NL * TPW];
 #pragma unroll
   for (int i = 0; i < NL * TPW; ++i) gacc[i] = zero4;
   const int kt0 = (wave / Gm::JG) * TK, jt0 = (wave % Gm::JG) * TJ;
 
-  // LDS tiles: see the one-kernel training step at width 64.  Chunk c (8
-  // rows, one 16-byte operand) of feature row f sits at c ^ (f % 16) ^
-  // 4 [f / 8 odd]; rows 4 g .. 4 g + 3 of block b go to chunk
-  // 4 (b / 2) + g, half (b % 2) ^ (g % 2), or with two blocks per wave both
-  // blocks' rows to chunk 4 wave + g in one 16-byte store.
-  auto dt_off = [&](int f, int c) { return f * LDT + ((c ^ (f & 15) ^ ((f >> 1) & 4)) << 3); };
-  auto put = [&](uint16_t* tile, int f, const f32x4 (&o)[NT]) {
-    if constexpr (NT == 2) {
-      *reinterpret_cast<u32x4*>(tile + dt_off(f, 4 * wave + lg)) =
-          u32x4{pack_bf16x2(o[0][0], o[0][1]), pack_bf16x2(o[0][2], o[0][3]),
-                pack_bf16x2(o[NT - 1][0], o[NT - 1][1]), pack_bf16x2(o[NT - 1][2], o[NT - 1][3])};
-    } else {
-      *reinterpret_cast<u32x2*>(tile + dt_off(f, 4 * (wave >> 1) + lg) + 4 * ((wave & 1) ^ (lg & 1))) =
-          u32x2{pack_bf16x2(o[0][0], o[0][1]), pack_bf16x2(o[0][2], o[0][3])};
-    }
-  };
+  uint32_t offK[TK], offJ[TJ];  // tile read offsets of the wave's pieces
+#pragma unroll
+  for (int t = 0; t < TK; ++t) offK[t] = RT::read_off(li, lg, kt0 + t);
+#pragma unroll
+  for (int t = 0; t < TJ; ++t) offJ[t] = RT::read_off(li, lg, jt0 + t);
 
   struct Rows {
     int64_t row0, vr;
@@ -141,7 +116,7 @@ __global__ __launch_bounds__(kBwdsWaves * 64) void bwds_kernel(const BwdsArgs a)
         dst[n][kb] = u32x4{lo.x, lo.y, up.x, up.y};
       }
   };
-  u32x4 ab[NL][NT][KBW];               // A of every layer of the segment, one tile ahead
+  u32x4 ab[NL][NT][KBW];               // A of every layer of the segment
   u32x4 cq[NT][KBW];                   // sine: cos of the next product's layer
   u32x4 dN[SEEDED ? 1 : NT][SEEDED ? 1 : KBW];  // the next tile's D_{hi+1}
   u32x4 gq[SEEDED ? NT : 1], oq[SEEDED ? NT : 1];  // seeded: its first strip's dY and C_L
@@ -187,7 +162,9 @@ __global__ __launch_bounds__(kBwdsWaves * 64) void bwds_kernel(const BwdsArgs a)
 
   const int G = gridDim.x;
   fetch_top(blockIdx.x);
-  static_for<0, XLATE ? NL - 1 : NL>([&](auto ic) { load_a(ic, blockIdx.x); });
+  static_for<0, AHEAD + 1>([&](auto ic) {
+    if constexpr (!XLATE || decltype(ic)::value != NL - 1) load_a(ic, blockIdx.x);
+  });
   drain_and_sync();  // weights in LDS
 
   for (int tile = blockIdx.x; tile < a.ntiles; tile += G) {
@@ -250,23 +227,8 @@ __global__ __launch_bounds__(kBwdsWaves * 64) void bwds_kernel(const BwdsArgs a)
       constexpr bool OUTL = TOP && i == 0;       // the output layer: SO strips of delta
       constexpr bool BOTL = BOT && i == NL - 1;  // layer 0: A is X, no further delta
       if constexpr (BOTL) mask_x_rows<NT, KBW>(in_dim, lg, ab[i]);
-      static_for<0, SW>([&](auto sc) {
-        constexpr int s = decltype(sc)::value;
-        const u32x4 sl = (s & 1) ? sel1 : sel0;
-        f32x4 o[NT];
-        if (!OUTL || s < SO) {
-#pragma unroll
-          for (int n = 0; n < NT; ++n) o[n] = mfma16(cur[n][s >> 1], sl, zero4);
-          put(DT, 16 * s + li, o);
-        }
-        // X in input order: k-block s / 2, half s % 2 gives lane (g, n)
-        // feature 32 (s / 2) + 8 (n / 4) + 4 (s % 2) + n % 4
-        if (!BOTL || 32 * (s >> 1) < in_dim) {
-#pragma unroll
-          for (int n = 0; n < NT; ++n) o[n] = mfma16(ab[i][n][s >> 1], sl, zero4);
-          put(AT, BOTL ? 32 * (s >> 1) + 8 * (li >> 2) + 4 * (s & 1) + (li & 3) : 16 * s + li, o);
-        }
-      });
+      RT::template put<NT, KBW>(DT, wave * NT * 16, li, lg, cur);
+      RT::template put<NT, KBW>(AT, wave * NT * 16, li, lg, ab[i]);
       __syncthreads();  // DT and AT hold the tile's rows
 
       constexpr int NG = KS * TPW, NS = BOTL ? 1 : SW;
@@ -279,25 +241,25 @@ __global__ __launch_bounds__(kBwdsWaves * 64) void bwds_kernel(const BwdsArgs a)
           constexpr int ks = q / TPW, u = (q % TPW) / TJ, v = q % TJ;
           if constexpr (q % TPW == 0) {
 #pragma unroll
-            for (int t = 0; t < TK; ++t)
-              ao[t] = *reinterpret_cast<const u32x4*>(AT + dt_off(16 * (kt0 + t) + li, 4 * ks + lg));
+            for (int t = 0; t < TK; ++t) ao[t] = RT::read(AT, offK[t], ks);
 #pragma unroll
             for (int t = 0; t < TJ; ++t)
-              if (!OUTL || jt0 + t < SO)
-                bo[t] = *reinterpret_cast<const u32x4*>(DT + dt_off(16 * (jt0 + t) + li, 4 * ks + lg));
+              if (!OUTL || ((jt0 + t) & ~1) < SO) bo[t] = RT::read(DT, offJ[t], ks);
           }
-          if (!OUTL || jt0 + v < SO)
+          if (!OUTL || ((jt0 + v) & ~1) < SO)  // pieces 2 kb, 2 kb + 1 hold strips 2 kb, 2 kb + 1
             gacc[i * TPW + u * TJ + v] = mfma16(ao[u], bo[v], gacc[i * TPW + u * TJ + v]);
         });
         if constexpr (!BOTL) {
           u32x4 af[KBW];
 #pragma unroll
-          for (int kb = 0; kb < KBW; ++kb) af[kb] = wl[(s * KBW + kb) * 64 + lane];
+          for (int kb = 0; kb < KBW; ++kb)
+            if (!OUTL || 2 * kb < SO) af[kb] = wl[(s * KBW + kb) * 64 + lane];
 #pragma unroll
           for (int n = 0; n < NT; ++n) {
             f32x4 acc = zero4;
 #pragma unroll
-            for (int kb = 0; kb < KBW; ++kb) acc = mfma16(af[kb], cur[n][kb], acc);
+            for (int kb = 0; kb < KBW; ++kb)
+              if (!OUTL || 2 * kb < SO) acc = mfma16(af[kb], cur[n][kb], acc);
             const u32x4 av = AC == BWDS_SINE ? cq[n][s >> 1] : ab[i][n][s >> 1];
             const u32x2 dv = (s & 1) ? u32x2{av.z, av.w} : u32x2{av.x, av.y};
             uint32_t p0, p1;
@@ -319,10 +281,11 @@ __global__ __launch_bounds__(kBwdsWaves * 64) void bwds_kernel(const BwdsArgs a)
         }
         __builtin_amdgcn_sched_barrier(0);
       });
-      // This layer's registers are free: the next tile's A, and the cos of
-      // the layer below (or of the next tile's top).  At width 128 the
-      // bottom's X is requested one layer ahead instead (register budget).
-      if constexpr (!(XLATE && BOTL)) load_a(ic, tile + G);
+      // The A that is needed AHEAD + 1 layers from here, of this tile or the
+      // next, and the cos of the layer below.  In long segments X is requested
+      // one layer ahead only (register budget).
+      if constexpr (!XLATE || (i + 1 + AHEAD) % NL != NL - 1)
+        load_a(std::integral_constant<int, (i + 1 + AHEAD) % NL>{}, i + 1 + AHEAD < NL ? tile : tile + G);
       if constexpr (XLATE && i == NL - 2) load_a(std::integral_constant<int, NL - 1>{}, tile);
       if constexpr (AC == BWDS_SINE) {
         if constexpr (i + 1 < NL && !(BOT && i + 1 == NL - 1)) load_cos(i + 1, tile);
@@ -388,10 +351,10 @@ __global__ __launch_bounds__(kBwdsWaves * 64) void bwds_kernel(const BwdsArgs a)
     for (int u = 0; u < TK; ++u)
 #pragma unroll
       for (int v = 0; v < TJ; ++v) {
-        const int j = 16 * (jt0 + v) + li;
+        const int j = chain_feature(16 * (jt0 + v) + li);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const int k = 16 * (kt0 + u) + 4 * lg + q;
+          const int p = 16 * (kt0 + u) + 4 * lg + q, k = l == 0 ? p : chain_feature(p);
           if (k < fi && j < fo) part[off + (int64_t)k * fo + j] = gacc[i * TPW + u * TJ + v][q];
         }
       }
@@ -399,13 +362,21 @@ __global__ __launch_bounds__(kBwdsWaves * 64) void bwds_kernel(const BwdsArgs a)
 }
 
 template <int W, int NL, bool TOP, bool BOT, bool SEEDED, int AC>
+struct BwdsKernel {
+  static constexpr auto kern = bwds_kernel<W, NL, TOP, BOT, SEEDED, AC>;
+  static constexpr size_t lds = BwdsGeom<W, NL>::lds_bytes();
+};
+template <int W, int NL, bool TOP, bool BOT, bool SEEDED, int AC>
+struct BwdsnKernel;  // widths 16 and 32, bwdsn_kernel.h
+
+template <int W, int NL, bool TOP, bool BOT, bool SEEDED, int AC>
 static hipError_t bwds_launch_t(const BwdsArgs& a, hipStream_t stream) {
-  using Gm = BwdsGeom<W, NL>;
-  auto kern = bwds_kernel<W, NL, TOP, BOT, SEEDED, AC>;
+  using K = std::conditional_t<(W <= 32), BwdsnKernel<W, NL, TOP, BOT, SEEDED, AC>,
+                               BwdsKernel<W, NL, TOP, BOT, SEEDED, AC>>;
   int occ = 0;  // raises the kernel's LDS limit
-  hipError_t e = kernel_occupancy(reinterpret_cast<const void*>(kern), kBwdsWaves * 64, Gm::lds_bytes(), &occ);
+  hipError_t e = kernel_occupancy(reinterpret_cast<const void*>(K::kern), kBwdsWaves * 64, K::lds, &occ);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(a.grid), dim3(kBwdsWaves * 64), Gm::lds_bytes(), stream, a);
+  hipLaunchKernelGGL(K::kern, dim3(a.grid), dim3(kBwdsWaves * 64), K::lds, stream, a);
   return hipGetLastError();
 }
 
@@ -418,12 +389,17 @@ static hipError_t bwds_by_act(const BwdsArgs& a, hipStream_t s) {
   }
 }
 
-// One segment of NL layers: the whole net, its top, its bottom or its middle.
-template <int W, int NL, int MULTI>
+// One segment of NL layers: the whole net, its top, its bottom or its
+// middle.  A training step reaches a whole net only where no one-kernel step
+// covers it (one matrix, or width 128).
+template <int W, int NL, bool MULTI>
 static hipError_t bwds_by_pos(const BwdsArgs& a, hipStream_t s) {
   const bool top = a.hi == a.L - 1, bot = a.lo == 0, seeded = a.dY != nullptr;
-  if (top && bot)
-    return seeded ? bwds_by_act<W, NL, true, true, true>(a, s) : bwds_by_act<W, NL, true, true, false>(a, s);
+  if (top && bot) {
+    if (seeded) return bwds_by_act<W, NL, true, true, true>(a, s);
+    if constexpr (W == 128 || NL == 1 || NL > kTrainfMaxL) return bwds_by_act<W, NL, true, true, false>(a, s);
+    return hipErrorNotSupported;
+  }
   if constexpr (MULTI) {
     if (top) return seeded ? bwds_by_act<W, NL, true, false, true>(a, s) : bwds_by_act<W, NL, true, false, false>(a, s);
     if (bot) return bwds_by_act<W, NL, false, true, false>(a, s);
@@ -432,8 +408,19 @@ static hipError_t bwds_by_pos(const BwdsArgs& a, hipStream_t s) {
   return hipErrorNotSupported;
 }
 
-// Longest segment.
-constexpr int bwds_max(int width) { return width == 128 ? 3 : 5; }
+// Longest segment, and the shortest of a net of several: with n segments of
+// at most bwds_max layers for more than (n - 1) bwds_max, each has at least
+// (bwds_max + 1) / 2.
+constexpr int bwds_max(int width) { return width == 128 ? 3 : (width == 64 ? 5 : (width == 32 ? 7 : 9)); }
+
+template <int W, int NL = 1>
+static hipError_t bwds_by_len(const BwdsArgs& a, hipStream_t s) {
+  if constexpr (NL <= bwds_max(W)) {
+    if (a.hi - a.lo + 1 == NL) return bwds_by_pos<W, NL, (2 * NL >= bwds_max(W))>(a, s);
+    return bwds_by_len<W, NL + 1>(a, s);
+  }
+  return hipErrorNotSupported;
+}
 
 template <int W>
 hipError_t launch_bwds_w(const BwdsArgs& a, hipStream_t s);

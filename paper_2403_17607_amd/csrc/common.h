@@ -73,28 +73,11 @@ inline int tile_rows(int width) {
   }
 }
 
-// Weight-gradient kernel geometry: each wave owns a TBK x TBJ block of
-// 16x16 output tiles; GK x GJ blocks cover G; KS waves split every chunk of
-// the batch; each wave runs KSW 32-row contraction steps per chunk.
-template <int W> struct WgCfg;
-// The chunk is CH = 32 KS KSW rows, so CH * W / 8 = 2048 16-byte units per
-// tensor at every width (eight per thread, all in flight at once).
-template <> struct WgCfg<16> { static constexpr int TBK = 1, TBJ = 1, GK = 1, GJ = 1, KS = 4, KSW = 8; };
-template <> struct WgCfg<32> { static constexpr int TBK = 2, TBJ = 2, GK = 1, GJ = 1, KS = 4, KSW = 4; };
-template <> struct WgCfg<64> { static constexpr int TBK = 2, TBJ = 2, GK = 2, GJ = 2, KS = 1, KSW = 8; };
-template <> struct WgCfg<128> { static constexpr int TBK = 4, TBJ = 4, GK = 2, GJ = 2, KS = 1, KSW = 4; };
-template <int W> constexpr int wg_chunk() { return 32 * WgCfg<W>::KS * WgCfg<W>::KSW; }
-inline int wgrad_chunk(int width) {
-  switch (width) {
-    case 16: return wg_chunk<16>();
-    case 32: return wg_chunk<32>();
-    case 64: return wg_chunk<64>();
-    default: return wg_chunk<128>();
-  }
-}
+// Rows per partial sum that the workspace size allows for (see ws_layout).
+inline int partial_rows(int width) { return 16384 / width; }
 
 constexpr int kMaxLossParts = 4096;  // upper bound on forward workgroups
-constexpr int kWgradTargetBlocks = 1024;
+constexpr int kPartialTarget = 1024;
 
 struct FwdArgs {
   const u32x4* packed;  // forward-packed weights, all layers
@@ -116,23 +99,6 @@ struct FwdArgs {
                         // stashA holds each strip transposed (see fwd_kernel.h)
 };
 
-struct BwdArgs {
-  const u32x4* packed;  // backward-packed weights, layers 1 .. L-1
-  const uint16_t* stashA;
-  const uint16_t* stashS;
-  uint16_t* deltaH;     // (L-1) x [M16][W]: delta_0 .. delta_{L-2}
-  uint16_t* deltaOut;   // [M16][OP]: delta_{L-1}
-  const float* cOut;    // [M16][OP] fp32 (seeded mode, nonlinear output)
-  const float* dY;      // [M][out_dim] (seeded mode)
-  const uint32_t* reluMask;  // (L-1) x [M16/16][64] ReLU mask words (ReLU nets)
-  const u32x4* packed0;  // backward-packed layer 0 (input gradient), read from global
-  float* dX;             // [M][in_dim] input gradient, or null
-  int64_t M, M16;
-  int in_dim, out_dim, L, out_act;
-  int ntiles, resident;
-  uint32_t layH_frags, total_frags;
-};
-
 // Fused backward pass with the weight gradients (bwdg_kernel): the deltas
 // never go to HBM; each workgroup keeps fixed slices of every layer's G in
 // registers across its row tiles and writes them once, as one partial.
@@ -145,13 +111,12 @@ struct BwdgArgs {
   const uint16_t* X;         // [M][in_dim]
   const uint16_t* stashA;    // (L-1) x [M16][W] tile images: a_1 .. a_{L-1}
   const uint32_t* reluMask;  // (L-1) x [M16/16][64] ReLU mask words (ReLU nets)
-  const uint16_t* stashS;    // (L-1) x [M16][W] bf16 cos of sine layers, or null
   const uint16_t* deltaOut;  // [M16][OP] output delta (training step)
   const float* cOut;         // [M16][OP] fp32 pre-activation (seeded, nonlinear output)
   const float* dY;           // [M][out_dim] (seeded mode)
   float* partial;            // [gridDim.x][params]
   int64_t M, M16, params;
-  int in_dim, out_dim, act, out_act;
+  int in_dim, out_dim, out_act;
   int ntiles;                // kBwdgRows-row tiles
   uint32_t layH_frags;       // 1 KiB fragments of one packed hidden layer
   int stash_t;               // stashA written transposed (FwdArgs::stash_t)
@@ -205,17 +170,6 @@ struct BwdsPlan {
   int nseg, base, rem, grid, ntiles;
 };
 
-struct WgradArgs {
-  const uint16_t* X;
-  const uint16_t* stashA;
-  const uint16_t* deltaH;
-  const uint16_t* deltaOut;
-  float* partial;       // [P][param_count]
-  int64_t M, M16, params;
-  int in_dim, out_dim, L;
-  int P, chunks_per_block;
-};
-
 // Fixed-order sum of the P weight-gradient partials: slice y (partials
 // [y P / S, (y+1) P / S)) is added in order, then the S slice sums in order
 // into G; the same kernel sums the loss partials.
@@ -254,16 +208,11 @@ struct OptArgs {
 // Host-side launchers (one per translation unit).  They return a HIP error.
 hipError_t launch_forward(int width, int act, int mode, const FwdArgs& a,
                           hipStream_t s, int* grid_out);
-hipError_t launch_backward(int width, int act, int seeded, const BwdArgs& a,
-                           hipStream_t s);
-hipError_t launch_wgrad(int width, const WgradArgs& a, hipStream_t s);
-// Fused backward pass and weight-gradient partials; *grid_out receives the
-// number of partials written.  hipErrorNotSupported when no instantiation
-// covers the net (the caller then runs the unfused kernels).
-hipError_t launch_backward_fused(int width, int L, int out_dim, int seeded, const BwdgArgs& a,
-                                 hipStream_t s, int* grid_out);
+// Fused backward pass and weight-gradient partials at width 128; *grid_out
+// receives the number of partials written.
+hipError_t launch_backward_fused(int L, int seeded, const BwdgArgs& a, hipStream_t s, int* grid_out);
 // Whether launch_backward_fused covers a net (host-side shape check only).
-bool backward_fused_supported(int width, int L, int act, int in_dim, int out_dim);
+bool backward_fused_supported(int width, int L, int act, int out_dim);
 // Fused training step; *grid_out receives the number of G and loss
 // partials written.  hipErrorNotSupported when it does not cover the net.
 hipError_t launch_train_fused(int width, int L, int act, int out_dim, const TrainfArgs& a,

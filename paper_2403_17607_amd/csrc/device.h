@@ -242,6 +242,117 @@ __device__ __forceinline__ void mask_x_rows(int in_dim, int lg, u32x4 (&x)[NT][K
   }
 }
 
+// The same in strip order: lane (g, i) of block n gets features
+// 16 s + 4 g .. + 3 of row 16 n + i (the order of a tile image's strips), as
+// two strips of one 32-feature operand (k-block kb: strips 2 kb, 2 kb + 1);
+// W = 16 has one strip, the other half is 0.
+typedef u32x2 u32x2_a2 __attribute__((aligned(2)));
+template <int W, int NT, int KBW>
+__device__ __forceinline__ void load_x_strips(const uint16_t* X, int64_t row0, int64_t M, int in_dim, int li, int lg,
+                                              u32x4 (&dst)[NT][KBW]) {
+  int64_t vr = M - row0;
+  vr = vr < 0 ? 0 : (vr > NT * 16 ? NT * 16 : vr);
+  const rsrc_t xr = make_rsrc(X + row0 * in_dim, vr * in_dim * 2);
+  const bool vec = (in_dim & 3) == 0;
+  const bool inside = (row0 + NT * 16) * in_dim + 4 <= M * in_dim;  // at most 3 past block NT - 1's end
+  const uint16_t* p = X + row0 * in_dim;
+  static_for<0, W / 16>([&](auto sc) {
+    constexpr int s = decltype(sc)::value;
+    const int f0 = 16 * s + 4 * lg;
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      u32x2 v;
+      if (vec) {
+        v = bload64(xr, f0 < in_dim ? (uint32_t)((li * in_dim + f0) * 2) : kOOB, (uint32_t)(n * 32 * in_dim));
+      } else if (inside) {
+        v = *reinterpret_cast<const u32x2_a2*>(p + (uint32_t)(n * 16 * in_dim) +
+                                               (uint32_t)(li * in_dim + (f0 < in_dim ? f0 : 0)));
+      } else {
+        uint32_t e[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          e[q] = bload16(xr, f0 + q < in_dim ? (uint32_t)((li * in_dim + f0 + q) * 2) : kOOB, (uint32_t)(n * 32 * in_dim));
+        v = u32x2{e[0] | (e[1] << 16), e[2] | (e[3] << 16)};
+      }
+      if constexpr (W == 16) {
+        dst[n][0] = u32x4{v.x, v.y, 0u, 0u};
+      } else if constexpr (s & 1) {
+        dst[n][s >> 1].z = v.x;
+        dst[n][s >> 1].w = v.y;
+      } else {
+        dst[n][s >> 1].x = v.x;
+        dst[n][s >> 1].y = v.y;
+      }
+    }
+  });
+}
+template <int W, int NT, int KBW>
+__device__ __forceinline__ void mask_x_strips(int in_dim, int lg, u32x4 (&x)[NT][KBW]) {
+  if ((in_dim & 3) == 0) return;
+#pragma unroll
+  for (int s = 0; s < W / 16; ++s) {
+    if (16 * s + 16 <= in_dim) continue;
+    const int v = in_dim - 16 * s - 4 * lg;  // features of this lane's piece
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const uint32_t m = v >= 2 * j + 2 ? 0xffffffffu : (v == 2 * j + 1 ? 0xffffu : 0u);
+#pragma unroll
+      for (int n = 0; n < NT; ++n) x[n][s >> 1][2 * (s & 1) + j] &= m;
+    }
+  }
+}
+
+// LDS tile of batch rows, [row][W] bf16, from which a contraction over the
+// batch reads its MFMA operands: such an operand needs eight rows of one
+// feature per lane, which ds_read_b64_tr_b16 gathers from row-major LDS (the
+// 16 lanes of a group read four rows of 16 values, 8 bytes each, and get back
+// four rows of one value each).  The waves store the operands they hold as
+// they are, one 16-byte chunk c = 4 kb + g per k-block and row, so bringing
+// a row block to the contraction's layout costs no arithmetic (against two
+// selection-matrix MFMAs and four conversions per pair of strips).
+// Position 8 c + e of a row holds, for activations and deltas (chain order),
+// feature chain_feature(8 c + e); for X (input order) feature 8 c + e.
+// A 16-value piece q of row r is stored at piece q ^ (r mod pieces) with its
+// two chunks swapped where the next bit of r is set: the 16-byte stores of
+// one chunk in 8 (16) rows and the reads of one piece in 4 rows per lane
+// group then touch distinct banks.
+template <int W>
+struct RowTile {
+  static constexpr int RB = W * 2, NQ = W / 16;  // bytes per row, pieces
+  static constexpr int QS = NQ == 8 ? 3 : 2;
+  static __device__ __forceinline__ uint32_t chunk_off(int row, int c) {
+    return (uint32_t)(row * RB + ((((c >> 1) ^ (row & (NQ - 1))) << 1) | ((c & 1) ^ ((row >> QS) & 1))) * 16);
+  }
+  // NT blocks of 16 rows from row0 on, as MFMA operands (lane (g, i): row i).
+  template <int NT, int KBW>
+  static __device__ __forceinline__ void put(uint8_t* tile, int row0, int li, int lg, const u32x4 (&x)[NT][KBW]) {
+#pragma unroll
+    for (int n = 0; n < NT; ++n)
+#pragma unroll
+      for (int kb = 0; kb < KBW; ++kb)
+        *reinterpret_cast<u32x4*>(tile + chunk_off(row0 + 16 * n + li, 4 * kb + lg)) = x[n][kb];
+  }
+  // This lane's byte offset for piece q of the first 16 rows.
+  static __device__ __forceinline__ uint32_t read_off(int li, int lg, int q) {
+    return chunk_off(4 * lg + (li >> 2), 2 * q + ((li >> 1) & 1)) + 8 * (li & 1);
+  }
+  static __device__ __forceinline__ u32x2 read4(const uint8_t* p) {
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    return __builtin_bit_cast(
+        u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(p)));
+  }
+  // Operand of 32-row step ks: lane (g, n) gets value n of the piece, rows
+  // 32 ks + 4 g + r in slots r and 32 ks + 16 + 4 g + r in slots 4 + r.
+  static __device__ __forceinline__ u32x4 read(const uint8_t* tile, uint32_t off, int ks) {
+    const u32x2 a = read4(tile + off + (32 * ks) * RB), b = read4(tile + off + (32 * ks + 16) * RB);
+    return u32x4{a.x, a.y, b.x, b.y};
+  }
+};
+// Feature at position p of a chain-order row.
+__device__ __forceinline__ int chain_feature(int p) {
+  return (p & ~31) + 16 * ((p >> 2) & 1) + 4 * ((p >> 3) & 3) + (p & 3);
+}
+
 // Asynchronous copy of nfrag 1 KiB fragments from global memory into LDS
 // with direct-to-LDS loads (no registers): wave w copies fragments w,
 // w + nwaves, ...; lane l of a load writes bytes 16 l .. 16 l + 15 of the

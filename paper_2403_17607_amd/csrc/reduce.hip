@@ -1,0 +1,131 @@
+// The fixed-order reduction of the per-workgroup partial weight gradients
+// and loss sums, and the weight packing.
+#include "device.h"
+
+namespace ffmlp {
+
+// Fixed-order sum of the P partials into G, one pass.  Block b owns
+// parameters 64 b .. 64 b + 63 and its wave y (of 16) adds slice y of the
+// partials, [y P / 16, (y + 1) P / 16), in order; the 16 slice sums are then
+// added in order through LDS.  The last block instead sums the loss
+// partials: thread t < 256 adds partials t, t + 256, ... in order, then a
+// fixed tree over those 256 threads.
+static_assert(kReduceSlices * 64 == 1024, "one wave per slice in a 1024-thread block");
+__global__ __launch_bounds__(1024) void reduce_kernel(const ReduceArgs a) {
+  __shared__ float part[kReduceSlices][64];
+  const int t = threadIdx.x;
+  if (blockIdx.x == gridDim.x - 1) {
+    float* lp = &part[0][0];  // 256 of its 1024 floats
+    if (t < 256) {
+      float s = 0.f;
+      for (int i = t; i < a.nloss; i += 256) s += a.lossPart[i];
+      lp[t] = s;
+    }
+    __syncthreads();
+    for (int h = 128; h > 0; h >>= 1) {
+      if (t < h) lp[t] += lp[t + h];
+      __syncthreads();
+    }
+    if (t == 0 && a.loss != nullptr) *a.loss = lp[0] * a.loss_scale;
+    return;
+  }
+  const int j = t & 63, y = t >> 6;
+  const int64_t e = (int64_t)blockIdx.x * 64 + j;
+  float s = 0.f;
+  if (e < a.params) {
+    const int p0 = (int)((int64_t)a.P * y / kReduceSlices);
+    const int p1 = (int)((int64_t)a.P * (y + 1) / kReduceSlices);
+    // Loads go out eight at a time, then are added in order: the same sum,
+    // without one memory latency per partial.
+    const float* src = a.partial + e;
+    int p = p0;
+    for (; p + 8 <= p1; p += 8) {
+      float v[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v[k] = src[(int64_t)(p + k) * a.params];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) s += v[k];
+    }
+    for (; p < p1; ++p) s += src[(int64_t)p * a.params];
+  }
+  part[y][j] = s;
+  __syncthreads();
+  if (t < 64 && e < a.params) {
+    float g = 0.f;
+#pragma unroll
+    for (int k = 0; k < kReduceSlices; ++k) g += part[k][t];
+    a.G[e] = g;
+  }
+}
+
+// One thread per packed bf16 element.  The buffer holds the forward
+// layers 0 .. L-1, then the backward layers 1 .. L-1, then the backward
+// layer 0 (for the input gradient), each as fragments
+// [strip][k-block][lane][slot]; see common.h for the two orientations and
+// the contraction orders.
+__global__ __launch_bounds__(256) void pack_kernel(const PackArgs a) {
+  const int64_t e0 = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (e0 >= a.total) return;
+  const int Wd = a.width, L = a.L;
+  auto fan_in = [&](int l) { return l == 0 ? a.in_dim : Wd; };
+  auto fan_out = [&](int l) { return l == L - 1 ? a.out_dim : Wd; };
+  // Locate the layer and orientation of element e0: forward layers
+  // 0 .. L-1, backward layers 1 .. L-1, then backward layer 0 (read only
+  // by the input-gradient step).  A segment holds strips(rows) fragments of
+  // 512 elements per k-block, rows being the fan_out (forward) or fan_in
+  // (backward) of its layer, so every hidden segment has the same size and
+  // the position follows in closed form, whatever the depth.
+  const int64_t per = (int64_t)((Wd + 31) / 32) * 512;  // one strip
+  const int64_t nW = per * ((Wd + 15) / 16);
+  const int64_t nO = per * ((a.out_dim + 15) / 16);
+  const int64_t nH = (int64_t)(L - 1) * nW;  // L - 1 segments of nW
+  int64_t e = e0;
+  int dir, l;
+  if (e < nH) {
+    dir = 0;
+    l = (int)(e / nW);
+    e -= (int64_t)l * nW;
+  } else if ((e -= nH) < nO) {
+    dir = 0;
+    l = L - 1;
+  } else if ((e -= nO) < nH) {
+    dir = 1;
+    l = 1 + (int)(e / nW);
+    e -= (int64_t)(l - 1) * nW;
+  } else {
+    e -= nH;  // < strips(in_dim) strips: e0 < total
+    dir = 1;
+    l = 0;
+  }
+  const int64_t woff = l == 0 ? 0 : (int64_t)a.in_dim * Wd + (int64_t)(l - 1) * Wd * Wd;
+  const int fi = fan_in(l), fo = fan_out(l);
+  const int kblocks = (Wd + 31) / 32;  // every layer is padded to the width's k-blocks
+  const int slot = (int)(e & 7), lane = (int)((e >> 3) & 63);
+  const int frag = (int)(e >> 9);
+  const int s = frag / kblocks, kb = frag - s * kblocks;
+  const int g = lane >> 4, row = 16 * s + (lane & 15);
+  int pos;  // contraction index the (g, slot) pair stands for
+  if (dir == 0 && l == 0)
+    pos = 32 * kb + 8 * g + slot;
+  else
+    pos = 32 * kb + (slot < 4 ? 4 * g + slot : 16 + 4 * g + (slot - 4));
+  int f, j;  // W_l[f][j]
+  if (dir == 0) { f = pos; j = row; } else { f = row; j = pos; }
+  uint16_t v = 0;
+  if (f < fi && j < fo) v = a.W[woff + (int64_t)f * fo + j];
+  a.dst[e0] = v;
+}
+
+hipError_t launch_reduce(const ReduceArgs& a, hipStream_t s) {
+  const int64_t blocks = (a.params + 63) / 64;  // plus one for the loss
+  hipLaunchKernelGGL(reduce_kernel, dim3((unsigned)blocks + 1), dim3(1024), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_pack(const PackArgs& a, hipStream_t s) {
+  if (a.total == 0) return hipSuccess;
+  hipLaunchKernelGGL(pack_kernel, dim3((unsigned)((a.total + 255) / 256)), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+}  // namespace ffmlp

@@ -277,17 +277,19 @@ def test_random_shapes_input_gradient(ffmlp, gpu, width, depth, in_dim, out_dim,
             seed=width + depth + in_dim + out_dim + M)
 
 
-@pytest.mark.parametrize("width,depth", [(64, 0), (64, 4), (64, 5), (64, 10), (128, 0), (128, 2), (128, 3), (128, 6)])
-@pytest.mark.parametrize("in_dim,out_dim,M,act,out_act", [(1, 2, 1, "relu", "sigmoid"),
-                                                          (63, 17, 257, "sigmoid", "linear"),
-                                                          (33, 64, 255, "sine", "relu"),
-                                                          (64, 3, 4001, "linear", "sine")])
-def test_segmented_backward(ffmlp, gpu, width, depth, in_dim, out_dim, M, act, out_act):
-    """The segmented backward (widths 64 and 128): one segment and several,
-    both segment lengths, each activation class, one row, a tile's edges, X
-    rows that no vector load fits (also where the last row's would pass the
-    end of X), output strips from one to all; seeded and from the training
-    forward, with and without dX."""
+@pytest.mark.parametrize("width,depth", [(16, 0), (16, 8), (16, 9), (16, 18), (32, 0), (32, 6), (32, 7), (32, 14),
+                                         (64, 0), (64, 4), (64, 5), (64, 10), (128, 0), (128, 2), (128, 3), (128, 6)])
+@pytest.mark.parametrize("in64,out64,M,act,out_act", [(1, 2, 1, "relu", "sigmoid"),
+                                                      (63, 17, 257, "sigmoid", "linear"),
+                                                      (33, 64, 255, "sine", "relu"),
+                                                      (64, 3, 4001, "linear", "sine")])
+def test_segmented_backward(ffmlp, gpu, width, depth, in64, out64, M, act, out_act):
+    """The segmented backward: one segment and several, the shortest and
+    longest lengths, each activation class, one row, a tile's edges, X rows
+    that no vector load fits (also where the last row's would pass the end
+    of X), output strips from one to all; seeded and from the training
+    forward, with and without dX.  in64 and out64 in 64ths of the width."""
+    in_dim, out_dim = max(1, in64 * width // 64 - (in64 == 63)), max(1, out64 * width // 64)
     dx_case(ffmlp, gpu, width, depth, in_dim, out_dim, M, act, out_act, seed=31)
     run_case(ffmlp, gpu, width, depth, in_dim, out_dim, M, act, out_act, seed=32)
 
