@@ -247,13 +247,14 @@ __device__ __forceinline__ void mask_x_rows(int in_dim, int lg, u32x4 (&x)[NT][K
 // two strips of one 32-feature operand (k-block kb: strips 2 kb, 2 kb + 1);
 // W = 16 has one strip, the other half is 0.
 typedef u32x2 u32x2_a2 __attribute__((aligned(2)));
-template <int W, int NT, int KBW>
+// VEC: in_dim is known to be a multiple of 4.
+template <int W, bool VEC, int NT, int KBW>
 __device__ __forceinline__ void load_x_strips(const uint16_t* X, int64_t row0, int64_t M, int in_dim, int li, int lg,
                                               u32x4 (&dst)[NT][KBW]) {
   int64_t vr = M - row0;
   vr = vr < 0 ? 0 : (vr > NT * 16 ? NT * 16 : vr);
   const rsrc_t xr = make_rsrc(X + row0 * in_dim, vr * in_dim * 2);
-  const bool vec = (in_dim & 3) == 0;
+  const bool vec = VEC || (in_dim & 3) == 0;
   const bool inside = (row0 + NT * 16) * in_dim + 4 <= M * in_dim;  // at most 3 past block NT - 1's end
   const uint16_t* p = X + row0 * in_dim;
   static_for<0, W / 16>([&](auto sc) {

@@ -72,8 +72,7 @@ __global__ __launch_bounds__(kTrainfWaves * 64) void trainf_kernel(const TrainfA
   const int64_t M = a.M;
   const int in_dim = a.in_dim, out_dim = a.out_dim, out_act = a.out_act;
   const int SO = (out_dim + 15) >> 4;
-  const bool xvec = VEC || (in_dim & 7) == 0;
-  const bool yvec = VEC || (out_dim & 3) == 0;
+  const bool yvec = (out_dim & 3) == 0;
 
   // Resident weights, both orientations (direct-to-LDS loads).
   stage_frags(smem, a.packedF, a.fwd_total, wave, NW, lane);
@@ -120,55 +119,32 @@ __global__ __launch_bounds__(kTrainfWaves * 64) void trainf_kernel(const TrainfA
   // 32 kb + 8 g .. + 7, the first layer's packing) and T of its output
   // strips (lane (g, i): row i, columns 16 s + 4 g .. + 3).
   u32x4 xin[NT][KBW], tq[NT][OS];
-  auto load_xt = [&](int tile) {
-    const Rows r = rows_of(tile);
-    if (xvec) {
+  auto load_x = [&](const Rows& r, u32x4 (&dst)[NT][KBW]) {
+    if constexpr (VEC) {
       const rsrc_t xr = make_rsrc(a.X + r.row0 * in_dim, r.vr * in_dim * 2);
 #pragma unroll
       for (int kb = 0; kb < KBW; ++kb) {
         const int f0 = kb * 32 + lg * 8;
         const uint32_t voff = f0 < in_dim ? (uint32_t)((li * in_dim + f0) * 2) : kOOB;
 #pragma unroll
-        for (int n = 0; n < NT; ++n) xin[n][kb] = bload128(xr, voff, (uint32_t)(n * 32 * in_dim));
+        for (int n = 0; n < NT; ++n) dst[n][kb] = bload128(xr, voff, (uint32_t)(n * 32 * in_dim));
       }
     } else {
-      // other input widths: one 2-byte load per feature (0 past in_dim or M)
-      const rsrc_t xr = make_rsrc(a.X + r.row0 * in_dim, r.vr * in_dim * 2);
-#pragma unroll
-      for (int kb = 0; kb < KBW; ++kb) {
-        const int f0 = kb * 32 + lg * 8;
-        uint32_t vo[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) vo[q] = f0 + q < in_dim ? (uint32_t)((li * in_dim + f0 + q) * 2) : kOOB;
-#pragma unroll
-        for (int n = 0; n < NT; ++n) {
-          uint32_t e[8];
-#pragma unroll
-          for (int q = 0; q < 8; ++q) e[q] = bload16(xr, vo[q], (uint32_t)(n * 32 * in_dim));
-          xin[n][kb] = u32x4{e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16),
-                             e[6] | (e[7] << 16)};
-        }
-      }
+      load_x_rows<NT, KBW>(a.X, r.row0, M, in_dim, li, lg, dst);
     }
+  };
+  auto load_xt = [&](int tile) {
+    const Rows r = rows_of(tile);
+    load_x(r, xin);
     const rsrc_t tr = make_rsrc(a.T + r.row0 * out_dim, r.vr * out_dim * 4);
 #pragma unroll
     for (int s = 0; s < OS; ++s) {
+      // 4-byte aligned; past out_dim the next row's values, which the
+      // epilogue's validity masks drop
       const int j0 = s * 16 + lg * 4;
-      if (yvec) {
-        const uint32_t eo = (j0 < out_dim) ? (uint32_t)(li * out_dim + j0) : kOOB / 4;
+      const uint32_t eo = (j0 < out_dim) ? (uint32_t)(li * out_dim + j0) : kOOB / 4;
 #pragma unroll
-        for (int n = 0; n < NT; ++n) tq[n][s] = bload128(tr, eo * 4, (uint32_t)(n * 64 * out_dim));
-      } else {
-        uint32_t vo[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) vo[q] = j0 + q < out_dim ? (uint32_t)((li * out_dim + j0 + q) * 4) : kOOB;
-#pragma unroll
-        for (int n = 0; n < NT; ++n) {
-          const uint32_t so = (uint32_t)(n * 64 * out_dim);
-          tq[n][s] = u32x4{bload32(tr, vo[0], so), bload32(tr, vo[1], so), bload32(tr, vo[2], so),
-                           bload32(tr, vo[3], so)};
-        }
-      }
+      for (int n = 0; n < NT; ++n) tq[n][s] = bload128(tr, eo * 4, (uint32_t)(n * 64 * out_dim));
     }
   };
 
@@ -188,6 +164,7 @@ __global__ __launch_bounds__(kTrainfWaves * 64) void trainf_kernel(const TrainfA
 
     // ---- forward: hidden activations a_1 .. a_{L-1} kept as strips
     // (lane (g, i) of block n: row 16 n + i, features 16 s + 4 g .. + 3).
+    if constexpr (!VEC) mask_x_rows<NT, KBW>(in_dim, lg, xin);
     u32x2 st[L - 1][NT][SW];
     u32x2 cs[CSL][NT][SW];  // sine: bf16 cos of the pre-activations
     // k-block kb of layer l's input for block n, chain order
@@ -311,37 +288,24 @@ __global__ __launch_bounds__(kTrainfWaves * 64) void trainf_kernel(const TrainfA
     // made after the last tile too (its rows are past M and read as 0): a
     // conditional one made the wait for the strips before G_0 drain it as
     // well (width 32 at 2^20 rows 54.6 -> 53.0 us).
-    u32x2 xs[NT][SW];
-    {
-      const rsrc_t xr = make_rsrc(a.X + r.row0 * in_dim, r.vr * in_dim * 2);
-#pragma unroll
-      for (int s = 0; s < SW; ++s) {
-        const int f0 = 16 * s + 4 * lg;
-        if (VEC || (in_dim & 3) == 0) {
-          const uint32_t voff = f0 < in_dim ? (uint32_t)((li * in_dim + f0) * 2) : kOOB;
-#pragma unroll
-          for (int n = 0; n < NT; ++n) xs[n][s] = bload64(xr, voff, (uint32_t)(n * 32 * in_dim));
-        } else {
-          uint32_t vo[4];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) vo[q] = f0 + q < in_dim ? (uint32_t)((li * in_dim + f0 + q) * 2) : kOOB;
-#pragma unroll
-          for (int n = 0; n < NT; ++n) {
-            uint32_t e[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) e[q] = bload16(xr, vo[q], (uint32_t)(n * 32 * in_dim));
-            xs[n][s] = u32x2{e[0] | (e[1] << 16), e[2] | (e[3] << 16)};
-          }
-        }
-      }
-    }
+    u32x4 xs4[NT][KBW];
+    load_x_strips<W, VEC, NT, KBW>(a.X, r.row0, M, in_dim, li, lg, xs4);
     load_xt(tile + G);
 
     // Layer l: G_l += A_l^T D_{l+1} over the wave's rows; for l >= 1 also
     // D_l = (D_{l+1} W_l^T) sigma'(a_l).
+    u32x2 xs[NT][SW];
     auto layer_step = [&](auto lc, const u32x4 (&cur)[NT][KBW], u32x4 (&nxt)[NT][KBW]) {
       constexpr int l = decltype(lc)::value;
       constexpr int SD = Gm::sd(l), GO = Gm::goff(l);
+      if constexpr (l == 0) {
+        if constexpr (!VEC) mask_x_strips<W, NT, KBW>(in_dim, lg, xs4);
+#pragma unroll
+        for (int n = 0; n < NT; ++n)
+#pragma unroll
+          for (int s = 0; s < SW; ++s)
+            xs[n][s] = s ? u32x2{xs4[n][0].z, xs4[n][0].w} : u32x2{xs4[n][0].x, xs4[n][0].y};
+      }
       const u32x2 (&ar)[NT][SW] = [&]() -> const u32x2 (&)[NT][SW] {
         if constexpr (l == 0) return xs;
         else return st[l - 1];
@@ -522,13 +486,15 @@ static hipError_t trainf_by_l(int L, const TrainfArgs& a, hipStream_t s, int* g)
   }
 }
 
-// VEC: X rows a multiple of 8 features and Y rows of 4 (16- and 8-byte
-// accesses only), the common case, compiled without the per-element paths:
-// measured at 2^20 rows with the output activation also fixed, width 16
-// 38.2 -> 32.5 us, width 32 63.3 -> 52.2 us, width 64 201.9 -> 182.7 us.
+// VEC: X rows a multiple of 8 features (aligned 16-byte loads only), the
+// common case, compiled without the unaligned loads of other widths.  Those,
+// one per lane and eight features, took the place of one load per feature:
+// 64-wide, in 37, out 7, 5 matrices, 300000 rows 83.4 -> 61.0 us, in 58, 2
+// sine matrices, 122313 rows 29.4 -> 19.2; 32-wide, in 27, 300000 rows 30.4
+// -> 25.1.
 template <int W, int OS, int ACT>
 static hipError_t trainf_by_vec(int L, const TrainfArgs& a, hipStream_t s, int* g) {
-  if (a.in_dim % 8 == 0 && a.out_dim % 4 == 0) return trainf_by_l<W, OS, ACT, true>(L, a, s, g);
+  if (a.in_dim % 8 == 0) return trainf_by_l<W, OS, ACT, true>(L, a, s, g);
   return trainf_by_l<W, OS, ACT, false>(L, a, s, g);
 }
 

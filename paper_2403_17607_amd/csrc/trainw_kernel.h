@@ -57,13 +57,12 @@ struct TrainwGeom {
                 "width-64 fused training step");
 };
 
-// Two blocks per wave where the registers allow it: one output strip, no
-// cos source, and at most 5 matrices (3 when X or Y need the per-element
-// paths).  Measured at 2^20 rows: image-like net (in 32, 2 hidden layers,
+// Two blocks per wave where the registers allow it: one output strip and no
+// cos source.  Measured at 2^20 rows: image-like net (in 32, 2 hidden layers,
 // sigmoid out 3) 110 -> 95 us, 5 matrices 181.5 -> 166 us.
 template <int L, int OS, int ACT, bool VEC>
 constexpr int trainw_nt() {
-  return (ACT != ACT_SINE && OS == 1 && L <= (VEC ? 5 : 3)) ? 2 : 1;
+  return (ACT != ACT_SINE && OS == 1) ? 2 : 1;
 }
 
 template <int L, int OS, int ACT, bool VEC>
@@ -82,8 +81,7 @@ __global__ __launch_bounds__(kTrainfWaves * 64) void trainw_kernel(const TrainfA
   const int64_t M = a.M;
   const int in_dim = a.in_dim, out_dim = a.out_dim, out_act = a.out_act;
   const int SO = (out_dim + 15) >> 4;
-  const bool xvec = VEC || (in_dim & 7) == 0;
-  const bool yvec = VEC || (out_dim & 3) == 0;
+  const bool yvec = (out_dim & 3) == 0;
 
   // Resident weights (direct-to-LDS loads, waited for below).
   stage_frags(smem, a.packedF, a.fwd_total, wave, NW, lane);
@@ -180,56 +178,35 @@ __global__ __launch_bounds__(kTrainfWaves * 64) void trainw_kernel(const TrainfA
   // 32 kb + 8 g .. + 7, the first layer's packing) and T of its output
   // strips (lane (g, i): row 16 n + i, columns 16 s + 4 g .. + 3).
   u32x4 xin[NT][KBW], tq[NT][OS];
-  auto load_xt = [&](int tile) {
-    const Rows r = rows_of(tile);
-    if (xvec) {
+  auto load_x = [&](const Rows& r, u32x4 (&dst)[NT][KBW]) {
+    if constexpr (VEC) {
       const rsrc_t xr = make_rsrc(a.X + r.row0 * in_dim, r.vr * in_dim * 2);
 #pragma unroll
       for (int kb = 0; kb < KBW; ++kb) {
         const int f0 = kb * 32 + lg * 8;
         const uint32_t voff = f0 < in_dim ? (uint32_t)((li * in_dim + f0) * 2) : kOOB;
 #pragma unroll
-        for (int n = 0; n < NT; ++n) xin[n][kb] = bload128(xr, voff, (uint32_t)(n * 32 * in_dim));
+        for (int n = 0; n < NT; ++n) dst[n][kb] = bload128(xr, voff, (uint32_t)(n * 32 * in_dim));
       }
     } else {
-      // other input widths: one 2-byte load per feature (0 past in_dim or M)
-      const rsrc_t xr = make_rsrc(a.X + r.row0 * in_dim, r.vr * in_dim * 2);
-#pragma unroll
-      for (int kb = 0; kb < KBW; ++kb) {
-        const int f0 = kb * 32 + lg * 8;
-#pragma unroll
-        for (int n = 0; n < NT; ++n) {
-          uint32_t e[8];
-#pragma unroll
-          for (int q = 0; q < 8; ++q)
-            e[q] = bload16(xr, f0 + q < in_dim ? (uint32_t)((li * in_dim + f0 + q) * 2) : kOOB,
-                           (uint32_t)(n * 32 * in_dim));
-          xin[n][kb] = u32x4{e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16),
-                             e[6] | (e[7] << 16)};
-        }
-      }
+      load_x_rows<NT, KBW>(a.X, r.row0, M, in_dim, li, lg, dst);
     }
+  };
+  auto load_xt = [&](int tile) {
+    const Rows r = rows_of(tile);
+    load_x(r, xin);
     const rsrc_t tr = make_rsrc(a.T + r.row0 * out_dim, r.vr * out_dim * 4);
 #pragma unroll
     for (int s = 0; s < OS; ++s) {
+      // 4-byte aligned; past out_dim the next row's values, which the
+      // epilogue's validity masks drop
       const int j0 = s * 16 + lg * 4;
-      if (yvec) {
-        const uint32_t eo = (j0 < out_dim) ? (uint32_t)(li * out_dim + j0) : kOOB / 4;
+      const uint32_t eo = (j0 < out_dim) ? (uint32_t)(li * out_dim + j0) : kOOB / 4;
 #pragma unroll
-        for (int n = 0; n < NT; ++n) tq[n][s] = bload128(tr, eo * 4, (uint32_t)(n * 64 * out_dim));
-      } else {
-#pragma unroll
-        for (int n = 0; n < NT; ++n) {
-          uint32_t t[4];
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-            t[q] = bload32(tr, j0 + q < out_dim ? (uint32_t)((li * out_dim + j0 + q) * 4) : kOOB,
-                           (uint32_t)(n * 64 * out_dim));
-          tq[n][s] = u32x4{t[0], t[1], t[2], t[3]};
-        }
-      }
+      for (int n = 0; n < NT; ++n) tq[n][s] = bload128(tr, eo * 4, (uint32_t)(n * 64 * out_dim));
     }
   };
+
   auto der = [&](uint32_t half) -> float {  // sigmoid a (1 - a); sine: the stored cos
     const float v = __uint_as_float(half);
     if constexpr (ACT == ACT_SIGMOID) return v * (1.f - v);
@@ -246,6 +223,7 @@ __global__ __launch_bounds__(kTrainfWaves * 64) void trainw_kernel(const TrainfA
     // ---- forward: a_1 .. a_{L-1} of the wave's rows in chain order (the
     // next layer's B operand; k-block kb holds strips 2 kb and 2 kb + 1).
     u32x4 ach[L - 1][NT][KBW];
+    if constexpr (!VEC) mask_x_rows<NT, KBW>(in_dim, lg, xin);
     u32x4 cch[CSL][NT][KBW];  // sine: bf16 cos of the pre-activations, same order
     static_for<0, L - 1>([&](auto lc) {
       constexpr int l = decltype(lc)::value;
@@ -358,30 +336,6 @@ __global__ __launch_bounds__(kTrainfWaves * 64) void trainw_kernel(const TrainfA
     // wave read these bytes at the start of the tile); then the next tile's
     // X and T into the buffers the forward no longer needs.
     u32x4 xc[NT][KBW];
-    auto load_xc = [&]() {
-      // input order, as for the forward (lane group g of block n: features
-      // 32 kb + 8 g .. + 7): 16 or 8 contiguous bytes per lane and row
-      const rsrc_t xr = make_rsrc(a.X + r.row0 * in_dim, r.vr * in_dim * 2);
-#pragma unroll
-      for (int n = 0; n < NT; ++n) {
-        const uint32_t so = (uint32_t)(n * 32 * in_dim);
-#pragma unroll
-        for (int kb = 0; kb < KBW; ++kb) {
-          const int f0 = 32 * kb + 8 * lg;
-          if (xvec) {
-            xc[n][kb] = bload128(xr, f0 < in_dim ? (uint32_t)((li * in_dim + f0) * 2) : kOOB, so);
-          } else {
-            uint32_t e[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q)
-              e[q] = bload16(xr, f0 + q < in_dim ? (uint32_t)((li * in_dim + f0 + q) * 2) : kOOB, so);
-            xc[n][kb] = u32x4{e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16),
-                              e[6] | (e[7] << 16)};
-          }
-        }
-      }
-    };
-
     // Layer l.  Phase 1: D_{l+1} (in `cur`) and A_l (this wave's rows)
     // transposed into DT and AT.  Phase 2 (after a barrier): the wave's G_l
     // slices over the tile's rows, interleaved strip by strip with
@@ -402,9 +356,10 @@ __global__ __launch_bounds__(kTrainfWaves * 64) void trainw_kernel(const TrainfA
       // as 0), so the wait for X before layer 0 counts it instead of
       // draining it.
       if constexpr (l == (L >= 5 ? 1 : L - 1)) {
-        load_xc();
+        load_x(r, xc);
         if constexpr (L < 5) load_xt(tile + G);
       }
+      if constexpr (!VEC && l == 0) mask_x_rows<NT, KBW>(in_dim, lg, xc);
       if constexpr (NT == 2) {
         static_for<0, SD>([&](auto sc) {
           constexpr int s = decltype(sc)::value;
@@ -588,10 +543,10 @@ static hipError_t trainw_by_l(int L, const TrainfArgs& a, hipStream_t s, int* g)
   }
 }
 
-// VEC: X rows a multiple of 8 features and Y rows of 4 (see trainf_by_vec).
+// VEC: X rows a multiple of 8 features (see trainf_by_vec).
 template <int OS, int ACT>
 static hipError_t trainw_by_vec(int L, const TrainfArgs& a, hipStream_t s, int* g) {
-  if (a.in_dim % 8 == 0 && a.out_dim % 4 == 0) return trainw_by_l<OS, ACT, true>(L, a, s, g);
+  if (a.in_dim % 8 == 0) return trainw_by_l<OS, ACT, true>(L, a, s, g);
   return trainw_by_l<OS, ACT, false>(L, a, s, g);
 }
 
