@@ -153,6 +153,19 @@ FwdArgs fwd_args(const mlp* h, const void* packed, const uint16_t* X, int64_t M)
   return a;
 }
 
+PackArgs pack_args(const mlp* h, const uint16_t* W, void* packed) {
+  const PackGeom g = pack_geom(h);
+  PackArgs a{};
+  a.W = W;
+  a.dst = static_cast<uint16_t*>(packed);
+  a.width = h->width;
+  a.in_dim = h->in_dim;
+  a.out_dim = h->out_dim;
+  a.L = n_mats(h);
+  a.total = (int64_t)(g.fwd_total + g.bwd_total + g.bwd0) * 512;
+  return a;
+}
+
 // Whether a backward pass of this net reads the ReLU mask words: only the
 // fused backward at width 128 (the others take relu' from the stashed
 // activations, which they read anyway).
@@ -418,15 +431,7 @@ int mlp_pack_weights(const mlp_t* h, const uint16_t* W, void* packed, void* stre
   if (!W || !packed) return fail(MLP_ERR_INVALID_ARG, "null weight or packed pointer");
   if (!aligned(W, 2) || !aligned(packed, 16))
     return fail(MLP_ERR_INVALID_ARG, "W must be 2-byte and packed 16-byte aligned");
-  PackArgs a{};
-  a.W = W;
-  a.dst = static_cast<uint16_t*>(packed);
-  a.width = h->width;
-  a.in_dim = h->in_dim;
-  a.out_dim = h->out_dim;
-  a.L = n_mats(h);
-  a.total = (int64_t)(mlp_packed_bytes(h) / 2);
-  hipError_t e = launch_pack(a, static_cast<hipStream_t>(stream));
+  hipError_t e = launch_pack(pack_args(h, W, packed), static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "pack kernel launch");
   return MLP_OK;
 }
@@ -441,10 +446,9 @@ int optim_step(const mlp_t* h, OptArgs a, void* packed, void* stream) {
     return fail(MLP_ERR_INVALID_ARG, "misaligned pointer (master, m, v, G: 4 bytes; W: 2; packed: 16)");
   if (!std::isfinite(a.lr)) return fail(MLP_ERR_INVALID_ARG, "lr is not finite");
   a.n = param_count(h);
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = launch_optim(a, s);
+  if (packed) a.pack = pack_args(h, a.W, packed);
+  hipError_t e = launch_optim(a, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "optimizer kernel launch");
-  if (packed) return mlp_pack_weights(h, a.W, packed, stream);
   return MLP_OK;
 }
 

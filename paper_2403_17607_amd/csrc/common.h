@@ -203,6 +203,7 @@ struct OptArgs {
   float lr, beta1, beta2, eps;
   float step_size;     // lr / (1 - beta1^t)
   float inv_sqrt_bc2;  // 1 / sqrt(1 - beta2^t)
+  PackArgs pack;       // packed buffer to rewrite (total 0: none)
 };
 
 // Host-side launchers (one per translation unit).  They return a HIP error.

@@ -1,6 +1,7 @@
 // The fixed-order reduction of the per-workgroup partial weight gradients
 // and loss sums, and the weight packing.
 #include "device.h"
+#include "pack.h"
 
 namespace ffmlp {
 
@@ -58,62 +59,12 @@ __global__ __launch_bounds__(1024) void reduce_kernel(const ReduceArgs a) {
   }
 }
 
-// One thread per packed bf16 element.  The buffer holds the forward
-// layers 0 .. L-1, then the backward layers 1 .. L-1, then the backward
-// layer 0 (for the input gradient), each as fragments
-// [strip][k-block][lane][slot]; see common.h for the two orientations and
-// the contraction orders.
+// One thread per packed bf16 element (pack.h has the layout).
 __global__ __launch_bounds__(256) void pack_kernel(const PackArgs a) {
-  const int64_t e0 = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (e0 >= a.total) return;
-  const int Wd = a.width, L = a.L;
-  auto fan_in = [&](int l) { return l == 0 ? a.in_dim : Wd; };
-  auto fan_out = [&](int l) { return l == L - 1 ? a.out_dim : Wd; };
-  // Locate the layer and orientation of element e0: forward layers
-  // 0 .. L-1, backward layers 1 .. L-1, then backward layer 0 (read only
-  // by the input-gradient step).  A segment holds strips(rows) fragments of
-  // 512 elements per k-block, rows being the fan_out (forward) or fan_in
-  // (backward) of its layer, so every hidden segment has the same size and
-  // the position follows in closed form, whatever the depth.
-  const int64_t per = (int64_t)((Wd + 31) / 32) * 512;  // one strip
-  const int64_t nW = per * ((Wd + 15) / 16);
-  const int64_t nO = per * ((a.out_dim + 15) / 16);
-  const int64_t nH = (int64_t)(L - 1) * nW;  // L - 1 segments of nW
-  int64_t e = e0;
-  int dir, l;
-  if (e < nH) {
-    dir = 0;
-    l = (int)(e / nW);
-    e -= (int64_t)l * nW;
-  } else if ((e -= nH) < nO) {
-    dir = 0;
-    l = L - 1;
-  } else if ((e -= nO) < nH) {
-    dir = 1;
-    l = 1 + (int)(e / nW);
-    e -= (int64_t)(l - 1) * nW;
-  } else {
-    e -= nH;  // < strips(in_dim) strips: e0 < total
-    dir = 1;
-    l = 0;
-  }
-  const int64_t woff = l == 0 ? 0 : (int64_t)a.in_dim * Wd + (int64_t)(l - 1) * Wd * Wd;
-  const int fi = fan_in(l), fo = fan_out(l);
-  const int kblocks = (Wd + 31) / 32;  // every layer is padded to the width's k-blocks
-  const int slot = (int)(e & 7), lane = (int)((e >> 3) & 63);
-  const int frag = (int)(e >> 9);
-  const int s = frag / kblocks, kb = frag - s * kblocks;
-  const int g = lane >> 4, row = 16 * s + (lane & 15);
-  int pos;  // contraction index the (g, slot) pair stands for
-  if (dir == 0 && l == 0)
-    pos = 32 * kb + 8 * g + slot;
-  else
-    pos = 32 * kb + (slot < 4 ? 4 * g + slot : 16 + 4 * g + (slot - 4));
-  int f, j;  // W_l[f][j]
-  if (dir == 0) { f = pos; j = row; } else { f = row; j = pos; }
-  uint16_t v = 0;
-  if (f < fi && j < fo) v = a.W[woff + (int64_t)f * fo + j];
-  a.dst[e0] = v;
+  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (e >= a.total) return;
+  const int64_t i = packed_param(a, e);
+  a.dst[e] = i >= 0 ? a.W[i] : (uint16_t)0;
 }
 
 hipError_t launch_reduce(const ReduceArgs& a, hipStream_t s) {

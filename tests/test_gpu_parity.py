@@ -419,6 +419,23 @@ def test_optimizer_steps_match_oracle(ffmlp, gpu):
     assert np.array_equal(f64(W), oracle.to_bf16(f64(master)))
 
 
+@pytest.mark.parametrize("width,depth,in_dim,out_dim", [(16, 0, 3, 5), (16, 2, 16, 1), (32, 1, 17, 31), (64, 5, 64, 64),
+                                                        (128, 0, 127, 128), (128, 3, 1, 17)])
+def test_optimizer_repacks_every_place(ffmlp, gpu, width, depth, in_dim, out_dim):
+    """The optimizer step re-packs in its own launch: from a buffer of
+    garbage, every weight and every padding element equals a fresh pack."""
+    net = ffmlp.FusedMLP(width, depth, in_dim, out_dim, "relu")
+    n = net.param_count()
+    master = datagen.uniform(3, datagen.STREAM_W, (n,)).to(gpu)
+    G = datagen.uniform(4, datagen.STREAM_AUX, (n,)).to(gpu)
+    m, v = torch.zeros_like(master), torch.zeros_like(master)
+    W = torch.empty(n, dtype=torch.bfloat16, device=gpu)
+    for step in (lambda p: net.adam_step(master, m, v, G, W, p, 1e-2), lambda p: net.sgd_step(master, G, W, p, 1e-2)):
+        packed = torch.full((net.packed_bytes(),), 0x5A, dtype=torch.uint8, device=gpu)
+        step(packed)
+        assert torch.equal(packed, net.pack(W))
+
+
 def test_adam_training_loop_matches_oracle(ffmlp, gpu):
     """Five training steps (train step, then Adam with re-packing) on the
     GPU against the same loop on the oracle: losses agree and fall."""
