@@ -226,7 +226,7 @@ __global__ __launch_bounds__(kBwdsWaves * 64, (W == 64 ? 4 : 2)) void bwds_kerne
       constexpr int i = decltype(ic)::value;
       constexpr bool OUTL = TOP && i == 0;       // the output layer: SO strips of delta
       constexpr bool BOTL = BOT && i == NL - 1;  // layer 0: A is X, no further delta
-      if constexpr (BOTL) mask_x_rows<NT, KBW>(in_dim, lg, ab[i]);
+      if constexpr (BOTL) mask_x_rows<NT, KBW>(a.X, r.row0, M, in_dim, li, lg, ab[i]);
       RT::template put<NT, KBW>(DT, wave * NT * 16, li, lg, cur);
       RT::template put<NT, KBW>(AT, wave * NT * 16, li, lg, ab[i]);
       __syncthreads();  // DT and AT hold the tile's rows

@@ -176,7 +176,7 @@ __global__ __launch_bounds__(kBwdsWaves * 64) void bwdsn_kernel(const BwdsArgs a
     auto layer_step = [&](auto ic, const u32x4 (&cur)[NT], u32x4 (&nxt)[NT]) {
       constexpr int i = decltype(ic)::value;
       constexpr bool BOTL = BOT && i == NL - 1;
-      if constexpr (BOTL) mask_x_strips<W, NT, 1>(in_dim, lg, ab[i]);
+      if constexpr (BOTL) mask_x_strips<W, NT, 1>(a.X, r.row0, M, in_dim, li, lg, ab[i]);
       u32x4 dop[SW];
 #pragma unroll
       for (int j = 0; j < SW; ++j) {

@@ -179,126 +179,175 @@ __device__ __forceinline__ void bstore128(u32x4 v, rsrc_t r, uint32_t voff, uint
 // A_1 = X of NT 16-row blocks from row0 on, in input order: lane (g, i) of
 // block n gets features 32 kb + 8 g .. + 7 of row 16 n + i.  in_dim a
 // multiple of 8: aligned 16-byte buffer loads, 0 past the row and past M.
-// Other widths: rows start at any 2-byte address, so each lane's eight
-// features still come in one 16-byte load, unaligned, which reads on into
-// the next row; mask_x_rows, called when the values are first used (the
-// loads stay in flight until then), clears what is past in_dim.  Only where
-// such a load would pass the end of X are the features loaded one by one.
-typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
 template <int NT, int KBW>
-__device__ __forceinline__ void load_x_rows(const uint16_t* X, int64_t row0, int64_t M, int in_dim, int li, int lg,
-                                            u32x4 (&dst)[NT][KBW]) {
+__device__ __forceinline__ void load_x_aligned(const uint16_t* X, int64_t row0, int64_t M, int in_dim, int li, int lg,
+                                               u32x4 (&dst)[NT][KBW]) {
   int64_t vr = M - row0;
   vr = vr < 0 ? 0 : (vr > NT * 16 ? NT * 16 : vr);
   const rsrc_t xr = make_rsrc(X + row0 * in_dim, vr * in_dim * 2);
-  if ((in_dim & 7) == 0) {
 #pragma unroll
-    for (int kb = 0; kb < KBW; ++kb) {
-      const int f0 = kb * 32 + lg * 8;
-      const uint32_t voff = f0 < in_dim ? (uint32_t)((li * in_dim + f0) * 2) : kOOB;
+  for (int kb = 0; kb < KBW; ++kb) {
+    const int f0 = kb * 32 + lg * 8;
+    const uint32_t voff = f0 < in_dim ? (uint32_t)((li * in_dim + f0) * 2) : kOOB;
 #pragma unroll
-      for (int n = 0; n < NT; ++n) dst[n][kb] = bload128(xr, voff, (uint32_t)(n * 32 * in_dim));
+    for (int n = 0; n < NT; ++n) dst[n][kb] = bload128(xr, voff, (uint32_t)(n * 32 * in_dim));
+  }
+}
+// Other widths: rows start at any 2-byte address, so a lane's P features
+// (P = 8, or 4 of a strip) come in one unaligned load.  It may read on into
+// the next row; a load that would pass the end of X is moved back to end
+// there.  x_piece_fix, called when the values are first used (the loads stay
+// in flight until then), shifts such a piece into place and clears what is
+// past in_dim or M.  XPieces holds what both need for a wave's rows.
+typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
+typedef u32x2 u32x2_a2 __attribute__((aligned(2)));
+template <int P>
+struct XPieces {
+  const uint16_t* p;  // first element of row0 (or, past M, of X's last P elements)
+  int rem;            // largest element offset from p that a load may start at
+  int rows;           // rows of X from row0 on, as far as they matter
+  bool tiny;          // X has fewer than P elements: loaded one by one
+  __device__ __forceinline__ XPieces(const uint16_t* X, int64_t row0, int64_t M, int in_dim, int max_rows) {
+    const int64_t left = M - row0;
+    rows = (int)(left < 0 ? 0 : (left > max_rows + P ? max_rows + P : left));
+    p = rows > 0 ? X + row0 * in_dim : X + M * in_dim - P;
+    rem = rows > 0 ? rows * in_dim - P : 0;
+    tiny = M * in_dim < P;
+  }
+};
+// One lane's P features, as P / 2 dwords, from feature f0 of row r (0-based
+// from row0).
+template <int P, typename V, typename VU>
+__device__ __forceinline__ V x_piece_load(const XPieces<P>& x, int r, int f0, int in_dim) {
+  if (x.tiny) {
+    V v = {};
+#pragma unroll 1
+    for (int q = P - 1; q >= 0; --q) {
+      const uint32_t e = r < x.rows && f0 + q < in_dim ? (uint32_t)x.p[r * in_dim + f0 + q] : 0u;
+#pragma unroll
+      for (int d = P / 2 - 1; d > 0; --d) v[d] = (v[d] << 16) | (v[d - 1] >> 16);
+      v[0] = (v[0] << 16) | e;
     }
-  } else if ((row0 + NT * 16) * in_dim + 8 <= M * in_dim) {
-    // the last element any lane reads is at most 7 past block NT - 1's end
-    const uint16_t* p = X + row0 * in_dim;
+    return v;
+  }
+  const int e = r * in_dim + (f0 < in_dim ? f0 : 0);
+  return *reinterpret_cast<const VU*>(x.p + (e < x.rem ? e : x.rem));
+}
+template <int P, typename V>
+__device__ __forceinline__ void x_piece_fix(const XPieces<P>& x, int r, int f0, int in_dim, bool tail, V& v) {
+  if (tail) {  // wave-uniform
+    const int e = r * in_dim + (f0 < in_dim ? f0 : 0), k = e - (e < x.rem ? e : x.rem);
 #pragma unroll
-    for (int kb = 0; kb < KBW; ++kb) {
-      const int f0 = kb * 32 + lg * 8;
-      const uint32_t eo = (uint32_t)(li * in_dim + (f0 < in_dim ? f0 : 0));
-#pragma unroll
-      for (int n = 0; n < NT; ++n)
-        dst[n][kb] = *reinterpret_cast<const u32x4_a2*>(p + (uint32_t)(n * 16 * in_dim) + eo);
+    for (int d = 0; d < P / 2; ++d) {
+      const uint32_t up = d + 1 < P / 2 ? v[d + 1 < P / 2 ? d + 1 : 0] : 0u;
+      v[d] = (k & 1) ? (v[d] >> 16) | (up << 16) : v[d];
     }
-  } else {
 #pragma unroll
-    for (int kb = 0; kb < KBW; ++kb) {
-      const int f0 = kb * 32 + lg * 8;
+    for (int h = 1; h < P / 2; h *= 2)
 #pragma unroll
-      for (int n = 0; n < NT; ++n) {
-        uint32_t e[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q)
-          e[q] = bload16(xr, f0 + q < in_dim ? (uint32_t)((li * in_dim + f0 + q) * 2) : kOOB, (uint32_t)(n * 32 * in_dim));
-        dst[n][kb] = u32x4{e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
-        __builtin_amdgcn_sched_barrier(0);  // one piece at a time: bounds the registers
+      for (int d = 0; d < P / 2; ++d) {
+        const uint32_t up = d + h < P / 2 ? v[d + h < P / 2 ? d + h : 0] : 0u;
+        v[d] = (k & (2 * h)) ? up : v[d];
       }
+#pragma unroll
+    for (int d = 0; d < P / 2; ++d) v[d] = (r < x.rows && k < P) ? v[d] : 0u;
+  }
+  const int n = in_dim - f0;  // features of this piece
+#pragma unroll
+  for (int d = 0; d < P / 2; ++d) v[d] &= n >= 2 * d + 2 ? 0xffffffffu : (n == 2 * d + 1 ? 0xffffu : 0u);
+}
+template <int NT, int KBW>
+__device__ __forceinline__ void load_x_unaligned(const uint16_t* X, int64_t row0, int64_t M, int in_dim, int li, int lg,
+                                                 u32x4 (&dst)[NT][KBW]) {
+  const XPieces<8> x(X, row0, M, in_dim, NT * 16);
+#pragma unroll
+  for (int kb = 0; kb < KBW; ++kb) {
+    if (32 * kb >= in_dim) {  // wave-uniform: nothing of this k-block to load
+#pragma unroll
+      for (int n = 0; n < NT; ++n) dst[n][kb] = u32x4{0u, 0u, 0u, 0u};
+      continue;
     }
+#pragma unroll
+    for (int n = 0; n < NT; ++n)
+      dst[n][kb] = x_piece_load<8, u32x4, u32x4_a2>(x, 16 * n + li, kb * 32 + lg * 8, in_dim);
   }
 }
 template <int NT, int KBW>
-__device__ __forceinline__ void mask_x_rows(int in_dim, int lg, u32x4 (&x)[NT][KBW]) {
+__device__ __forceinline__ void load_x_rows(const uint16_t* X, int64_t row0, int64_t M, int in_dim, int li, int lg,
+                                            u32x4 (&dst)[NT][KBW]) {
+  if ((in_dim & 7) == 0) load_x_aligned<NT, KBW>(X, row0, M, in_dim, li, lg, dst);
+  else load_x_unaligned<NT, KBW>(X, row0, M, in_dim, li, lg, dst);
+}
+// Completes load_x_unaligned (nothing to do for multiples of 8).
+template <int NT, int KBW>
+__device__ __forceinline__ void mask_x_rows(const uint16_t* X, int64_t row0, int64_t M, int in_dim, int li, int lg,
+                                            u32x4 (&v)[NT][KBW]) {
   if ((in_dim & 7) == 0) return;
+  const XPieces<8> x(X, row0, M, in_dim, NT * 16);
+  // past the end of X only in the last wave tile
+  const bool tail = !x.tiny && (x.rows < NT * 16 || x.rem < (NT * 16 - 1) * in_dim + ((in_dim - 1) & ~7));
 #pragma unroll
   for (int kb = 0; kb < KBW; ++kb) {
-    if (32 * kb + 32 <= in_dim) continue;
-    const int v = in_dim - 32 * kb - 8 * lg;  // features of this lane's piece
+    if (32 * kb >= in_dim || (!tail && 32 * kb + 32 <= in_dim)) continue;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const uint32_t m = v >= 2 * j + 2 ? 0xffffffffu : (v == 2 * j + 1 ? 0xffffu : 0u);
-#pragma unroll
-      for (int n = 0; n < NT; ++n) x[n][kb][j] &= m;
-    }
+    for (int n = 0; n < NT; ++n) x_piece_fix<8>(x, 16 * n + li, kb * 32 + lg * 8, in_dim, tail, v[n][kb]);
   }
 }
 
 // The same in strip order: lane (g, i) of block n gets features
 // 16 s + 4 g .. + 3 of row 16 n + i (the order of a tile image's strips), as
 // two strips of one 32-feature operand (k-block kb: strips 2 kb, 2 kb + 1);
-// W = 16 has one strip, the other half is 0.
-typedef u32x2 u32x2_a2 __attribute__((aligned(2)));
-// VEC: in_dim is known to be a multiple of 4.
+// W = 16 has one strip, the other half is 0.  VEC: in_dim is known to be a
+// multiple of 4.
 template <int W, bool VEC, int NT, int KBW>
 __device__ __forceinline__ void load_x_strips(const uint16_t* X, int64_t row0, int64_t M, int in_dim, int li, int lg,
                                               u32x4 (&dst)[NT][KBW]) {
-  int64_t vr = M - row0;
-  vr = vr < 0 ? 0 : (vr > NT * 16 ? NT * 16 : vr);
-  const rsrc_t xr = make_rsrc(X + row0 * in_dim, vr * in_dim * 2);
-  const bool vec = VEC || (in_dim & 3) == 0;
-  const bool inside = (row0 + NT * 16) * in_dim + 4 <= M * in_dim;  // at most 3 past block NT - 1's end
-  const uint16_t* p = X + row0 * in_dim;
-  static_for<0, W / 16>([&](auto sc) {
+  auto put = [&](int n, auto sc, u32x2 v) {
     constexpr int s = decltype(sc)::value;
-    const int f0 = 16 * s + 4 * lg;
-#pragma unroll
-    for (int n = 0; n < NT; ++n) {
-      u32x2 v;
-      if (vec) {
-        v = bload64(xr, f0 < in_dim ? (uint32_t)((li * in_dim + f0) * 2) : kOOB, (uint32_t)(n * 32 * in_dim));
-      } else if (inside) {
-        v = *reinterpret_cast<const u32x2_a2*>(p + (uint32_t)(n * 16 * in_dim) +
-                                               (uint32_t)(li * in_dim + (f0 < in_dim ? f0 : 0)));
-      } else {
-        uint32_t e[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          e[q] = bload16(xr, f0 + q < in_dim ? (uint32_t)((li * in_dim + f0 + q) * 2) : kOOB, (uint32_t)(n * 32 * in_dim));
-        v = u32x2{e[0] | (e[1] << 16), e[2] | (e[3] << 16)};
-      }
-      if constexpr (W == 16) {
-        dst[n][0] = u32x4{v.x, v.y, 0u, 0u};
-      } else if constexpr (s & 1) {
-        dst[n][s >> 1].z = v.x;
-        dst[n][s >> 1].w = v.y;
-      } else {
-        dst[n][s >> 1].x = v.x;
-        dst[n][s >> 1].y = v.y;
-      }
+    if constexpr (W == 16) {
+      dst[n][0] = u32x4{v.x, v.y, 0u, 0u};
+    } else if constexpr (s & 1) {
+      dst[n][s >> 1].z = v.x;
+      dst[n][s >> 1].w = v.y;
+    } else {
+      dst[n][s >> 1].x = v.x;
+      dst[n][s >> 1].y = v.y;
     }
-  });
+  };
+  if (VEC || (in_dim & 3) == 0) {
+    int64_t vr = M - row0;
+    vr = vr < 0 ? 0 : (vr > NT * 16 ? NT * 16 : vr);
+    const rsrc_t xr = make_rsrc(X + row0 * in_dim, vr * in_dim * 2);
+    static_for<0, W / 16>([&](auto sc) {
+      const int f0 = 16 * decltype(sc)::value + 4 * lg;
+#pragma unroll
+      for (int n = 0; n < NT; ++n)
+        put(n, sc, bload64(xr, f0 < in_dim ? (uint32_t)((li * in_dim + f0) * 2) : kOOB, (uint32_t)(n * 32 * in_dim)));
+    });
+  } else {
+    const XPieces<4> x(X, row0, M, in_dim, NT * 16);
+    static_for<0, W / 16>([&](auto sc) {
+#pragma unroll
+      for (int n = 0; n < NT; ++n)
+        put(n, sc, x_piece_load<4, u32x2, u32x2_a2>(x, 16 * n + li, 16 * decltype(sc)::value + 4 * lg, in_dim));
+    });
+  }
 }
 template <int W, int NT, int KBW>
-__device__ __forceinline__ void mask_x_strips(int in_dim, int lg, u32x4 (&x)[NT][KBW]) {
+__device__ __forceinline__ void mask_x_strips(const uint16_t* X, int64_t row0, int64_t M, int in_dim, int li, int lg,
+                                              u32x4 (&v)[NT][KBW]) {
   if ((in_dim & 3) == 0) return;
+  const XPieces<4> x(X, row0, M, in_dim, NT * 16);
+  const bool tail = !x.tiny && (x.rows < NT * 16 || x.rem < (NT * 16 - 1) * in_dim + ((in_dim - 1) & ~3));
 #pragma unroll
   for (int s = 0; s < W / 16; ++s) {
-    if (16 * s + 16 <= in_dim) continue;
-    const int v = in_dim - 16 * s - 4 * lg;  // features of this lane's piece
+    if (!tail && 16 * s + 16 <= in_dim) continue;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const uint32_t m = v >= 2 * j + 2 ? 0xffffffffu : (v == 2 * j + 1 ? 0xffffu : 0u);
-#pragma unroll
-      for (int n = 0; n < NT; ++n) x[n][s >> 1][2 * (s & 1) + j] &= m;
+    for (int n = 0; n < NT; ++n) {
+      u32x2 t = {v[n][s >> 1][2 * (s & 1)], v[n][s >> 1][2 * (s & 1) + 1]};
+      x_piece_fix<4>(x, 16 * n + li, 16 * s + 4 * lg, in_dim, tail, t);
+      v[n][s >> 1][2 * (s & 1)] = t.x;
+      v[n][s >> 1][2 * (s & 1) + 1] = t.y;
     }
   }
 }

@@ -62,11 +62,11 @@ __device__ __forceinline__ void strip_product(const u32x4 (&af)[KBW], const u32x
 // the fragment reads per row double, a quarter of LDS bandwidth at the full
 // MFMA rate).  Measured at 2^20 rows: 5 matrices 112.1 -> 106.5 us, depth 16
 // with streamed weights 494.6 -> 474.1 us.  The even-L fused loop (FU 2)
-// needs more registers than the 128 that 4 waves per SIMD leave and runs 12
-// waves (97.7 -> 93.5 us for 4 matrices).
-template <int W, int MODE, bool SMALL = false, int FU = 0>
+// needs more registers than the 128 that 4 waves per SIMD leave, as do the
+// unaligned X loads (XU), and runs 12 waves (97.7 -> 93.5 us for 4 matrices).
+template <int W, int MODE, bool SMALL = false, int FU = 0, int XU = 0>
 constexpr int fwd_waves() {
-  if constexpr (W == 128 && MODE == FWD_INFER && !SMALL) return FU == 2 ? 12 : 16;
+  if constexpr (W == 128 && MODE == FWD_INFER && !SMALL) return (FU == 2 || XU == 1) ? 12 : 16;
   return (SMALL || (W <= 32 && MODE == FWD_INFER)) ? 8 : TileCfg<W>::NW;
 }
 // 16-row blocks per wave.
@@ -85,9 +85,10 @@ constexpr int fwd_nt() {
 // matrix cores itself (8 MFMAs and their conversions per layer and wave,
 // on its critical path), where the forward, bound by HBM, has them to
 // spare.  Same bytes, same addresses.
-template <int W, int ACT, int MODE, int FU, bool RES, bool SMALL = false, bool LIN = false, bool TST = false>
-__global__ __launch_bounds__((fwd_waves<W, MODE, SMALL, FU>() * 64)) void fwd_kernel(const FwdArgs a) {
-  constexpr int NT = fwd_nt<W, MODE, SMALL, FU>(), NW = fwd_waves<W, MODE, SMALL, FU>();
+template <int W, int ACT, int MODE, int FU, bool RES, bool SMALL = false, bool LIN = false, bool TST = false,
+          int XU = 0>
+__global__ __launch_bounds__((fwd_waves<W, MODE, SMALL, FU, XU>() * 64)) void fwd_kernel(const FwdArgs a) {
+  constexpr int NT = fwd_nt<W, MODE, SMALL, FU>(), NW = fwd_waves<W, MODE, SMALL, FU, XU>();
   constexpr int KBW = (W + 31) / 32, SW = W / 16;
   extern __shared__ u32x4 smem[];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -95,10 +96,8 @@ __global__ __launch_bounds__((fwd_waves<W, MODE, SMALL, FU>() * 64)) void fwd_ke
   const int li = lane & 15, lg = lane >> 4;
   const int L = a.L, in_dim = a.in_dim, out_dim = a.out_dim;
   const int64_t M = a.M;
-  const int KB0 = (in_dim + 31) >> 5;
   const int SO = (out_dim + 15) >> 4;
   const int OP = SO * 16;
-  const bool xvec = (in_dim & 7) == 0;
   const bool yvec = (out_dim & 3) == 0;
   const int out_act = LIN ? (int)ACT_LINEAR : a.out_act;
   static_assert(!TST || (MODE == FWD_TRAIN && NT % 2 == 0), "transposed stash: training forward, block pairs");
@@ -155,24 +154,16 @@ __global__ __launch_bounds__((fwd_waves<W, MODE, SMALL, FU>() * 64)) void fwd_ke
     if (l + 1 < L) stage_layer(l + 1, step + 1);
     else if (tile + G < a.ntiles) stage_layer(0, step + 1);
   };
-  // A_1 = X of a wave tile, in input order: lane group g takes features
-  // 32 kb + 8 g .. + 7.
-  // With VEC (in_dim a multiple of 8) each lane reads 16-byte pieces.
-  auto load_x_t = [&](auto VECc, int tile, u32x4 (&dst)[NT][KBW]) {
+  // A_1 = X of a wave tile, in input order.  XU 0: in_dim a multiple of 8,
+  // aligned loads.  XU 1: unaligned loads, and the values past in_dim are
+  // cleared when the tile starts (the other loads give 0 there).  XU 2: one
+  // load per feature.
+  auto load_x = [&](int tile, u32x4 (&dst)[NT][KBW]) {
     const int64_t r0 = (((int64_t)tile * NW + wave) * NT) * 16;
-    int64_t vr = M - r0;
-    vr = vr < 0 ? 0 : (vr > NT * 16 ? NT * 16 : vr);
-    if constexpr (decltype(VECc)::value) {
-      // per-lane byte offset inside a 16-row block; the block goes in the
-      // scalar offset
-      const rsrc_t xr = make_rsrc(a.X + r0 * in_dim, vr * in_dim * 2);
-#pragma unroll
-      for (int kb = 0; kb < KBW; ++kb) {
-        const int f0 = kb * 32 + lg * 8;
-        const uint32_t voff = (kb < KB0 && f0 < in_dim) ? (uint32_t)((li * in_dim + f0) * 2) : kOOB;
-#pragma unroll
-        for (int n = 0; n < NT; ++n) dst[n][kb] = bload128(xr, voff, (uint32_t)(n * 32 * in_dim));
-      }
+    if constexpr (XU == 0) {
+      load_x_aligned<NT, KBW>(a.X, r0, M, in_dim, li, lg, dst);
+    } else if constexpr (XU == 1) {
+      load_x_unaligned<NT, KBW>(a.X, r0, M, in_dim, li, lg, dst);
     } else {
 #pragma unroll
       for (int n = 0; n < NT; ++n) {
@@ -181,7 +172,7 @@ __global__ __launch_bounds__((fwd_waves<W, MODE, SMALL, FU>() * 64)) void fwd_ke
         for (int kb = 0; kb < KBW; ++kb) {
           const int f0 = kb * 32 + lg * 8;
           uint32_t e[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
-          if (kb < KB0 && m < M && f0 < in_dim) {
+          if (m < M && f0 < in_dim) {
             const uint16_t* xp = a.X + m * in_dim + f0;
 #pragma unroll
             for (int q = 0; q < 8; ++q) e[q] = (f0 + q < in_dim) ? (uint32_t)xp[q] : 0u;
@@ -192,11 +183,6 @@ __global__ __launch_bounds__((fwd_waves<W, MODE, SMALL, FU>() * 64)) void fwd_ke
       }
     }
   };
-  auto load_x = [&](int tile, u32x4 (&dst)[NT][KBW]) {
-    if (xvec) load_x_t(std::true_type{}, tile, dst);
-    else load_x_t(std::false_type{}, tile, dst);
-  };
-  auto load_xv = [&](int tile, u32x4 (&dst)[NT][KBW]) { load_x_t(std::true_type{}, tile, dst); };
   // Narrow nets have registers to spare for the X of later tiles: each
   // wave requests X two tiles ahead (two buffers, used in turn by a tile
   // loop unrolled by two).
@@ -208,9 +194,9 @@ __global__ __launch_bounds__((fwd_waves<W, MODE, SMALL, FU>() * 64)) void fwd_ke
   // activation buffer is free during those two layers.  The next tile's X
   // is requested into it there, hidden behind that work.
   // The launcher picks FU 1 or 2 only for inference with every layer
-  // resident, L >= 2, SO == 1 and in_dim a multiple of 8.
-  // Other inference nets of these widths (FU 3, 4; L >= 2, in_dim a
-  // multiple of 8) keep the layers apart, and the next tile's X is
+  // resident, L >= 2 and SO == 1.
+  // Other inference nets of these widths (FU 3, 4; L >= 2) keep the layers
+  // apart, and the next tile's X is
   // requested into the activation buffer the output layer does not read,
   // hidden behind that layer.
   constexpr bool FUSE = FU == 1 || FU == 2;
@@ -222,7 +208,7 @@ __global__ __launch_bounds__((fwd_waves<W, MODE, SMALL, FU>() * 64)) void fwd_ke
     if ((int)blockIdx.x < a.ntiles) load_x(blockIdx.x, xq0);
     if ((int)blockIdx.x + G < a.ntiles) load_x(blockIdx.x + G, xq1);
   } else if constexpr (FUSE || OXP) {
-    if ((int)blockIdx.x < a.ntiles) load_xv(blockIdx.x, actA);
+    if ((int)blockIdx.x < a.ntiles) load_x(blockIdx.x, actA);
   }
   drain_and_sync();  // weights (the first layer, when streaming) in LDS
 
@@ -263,6 +249,7 @@ __global__ __launch_bounds__((fwd_waves<W, MODE, SMALL, FU>() * 64)) void fwd_ke
     } else if constexpr (!F && !OXP) {
       load_x(tile, bx);
     }
+    if constexpr (XU == 1) mask_x_rows<NT, KBW>(a.X, row0, M, in_dim, li, lg, bx);
 
     // Hidden layer l: out = bf16(sigma(in W_l)) in the next layer's chain
     // order (see common.h).  P is the layer's parity within its pair; the
@@ -445,7 +432,7 @@ __global__ __launch_bounds__((fwd_waves<W, MODE, SMALL, FU>() * 64)) void fwd_ke
         stage_next(l, tile);
       }
       if constexpr (OXP) {
-        if (tile + G < a.ntiles) load_xv(tile + G, nx);
+        if (tile + G < a.ntiles) load_x(tile + G, nx);
       }
       for (int s = 0; s < SO; ++s) {
         u32x4 af[KBW];
@@ -466,7 +453,7 @@ __global__ __launch_bounds__((fwd_waves<W, MODE, SMALL, FU>() * 64)) void fwd_ke
     auto last = [&](const u32x4 (&in)[NT][KBW], u32x4 (&nx)[NT][KBW]) {
       const u32x4* wl = smem + (size_t)layer_off(L - 2) * 64;
       const u32x4* wo = smem + (size_t)layer_off(L - 1) * 64;
-      if (tile + G < a.ntiles) load_xv(tile + G, nx);
+      if (tile + G < a.ntiles) load_x(tile + G, nx);
       f32x4 yacc[NT];
 #pragma unroll
       for (int n = 0; n < NT; ++n) yacc[n] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -587,17 +574,17 @@ struct FwdPick {
   int threads;
   int64_t rows;
 };
-template <int W, int ACT, int MODE, int FU, bool RES, bool SMALL = false, bool LIN = false, bool TST = false>
+template <int W, int ACT, int MODE, int FU, bool RES, bool SMALL, bool LIN, bool TST, int XU>
 static FwdPick fwd_pick() {
-  constexpr int NW = fwd_waves<W, MODE, SMALL, FU>(), NT = fwd_nt<W, MODE, SMALL, FU>();
-  return FwdPick{fwd_kernel<W, ACT, MODE, FU, RES, SMALL, LIN, TST>, NW * 64, (int64_t)NW * NT * 16};
+  constexpr int NW = fwd_waves<W, MODE, SMALL, FU, XU>(), NT = fwd_nt<W, MODE, SMALL, FU>();
+  return FwdPick{fwd_kernel<W, ACT, MODE, FU, RES, SMALL, LIN, TST, XU>, NW * 64, (int64_t)NW * NT * 16};
 }
 
 // LIN: the output activation is linear (the common case) and fixed at
 // compile time.  With a runtime output activation the epilogue switches per
 // element, which cost 12% of width-16 inference at 2^20 rows (17.9 -> 15.7
 // us) and 1-2% at the other widths.
-template <int W, int ACT, int MODE, bool LIN>
+template <int W, int ACT, int MODE, bool LIN, int XU>
 static hipError_t launch_t(const FwdArgs& a0, hipStream_t stream, int* grid_out) {
   FwdArgs a = a0;
   DeviceInfo di;
@@ -613,30 +600,48 @@ static hipError_t launch_t(const FwdArgs& a0, hipStream_t stream, int* grid_out)
   // (1297 against 1334 us for the whole step), so it keeps 1 KiB spare.
   a.resident = res_bytes + (MODE == FWD_INFER ? 0 : 1024) <= (size_t)di.max_lds ? 1 : 0;
   const size_t lds = a.resident ? res_bytes : (size_t)2 * maxf * 1024;
-  FwdPick pk = a.resident ? fwd_pick<W, ACT, MODE, 0, true, false, LIN>() : fwd_pick<W, ACT, MODE, 0, false, false, LIN>();
+  const bool res = a.resident != 0, odd = (a.L & 1) != 0;
+  FwdPick pk = res ? fwd_pick<W, ACT, MODE, 0, true, false, LIN, false, XU>()
+                   : fwd_pick<W, ACT, MODE, 0, false, false, LIN, false, XU>();
   if constexpr (W == 128 && MODE == FWD_TRAIN) {
     if (a.stash_t)
-      pk = a.resident ? fwd_pick<W, ACT, MODE, 0, true, false, LIN, true>()
-                      : fwd_pick<W, ACT, MODE, 0, false, false, LIN, true>();
+      pk = res ? fwd_pick<W, ACT, MODE, 0, true, false, LIN, true, XU>()
+               : fwd_pick<W, ACT, MODE, 0, false, false, LIN, true, XU>();
   } else {
     if (a.stash_t) return hipErrorInvalidValue;  // only the width-128 training forward writes it
   }
-  if constexpr (MODE == FWD_INFER && W >= 64) {
-    if (a.resident && a.L >= 2 && SO == 1 && (a.in_dim % 8) == 0)
-      pk = (a.L & 1) ? fwd_pick<W, ACT, MODE, 1, true, false, LIN>() : fwd_pick<W, ACT, MODE, 2, true, false, LIN>();
-    else if (a.L >= 2 && (a.in_dim % 8) == 0)
-      pk = a.resident ? ((a.L & 1) ? fwd_pick<W, ACT, MODE, 4, true, false, LIN>()
-                                   : fwd_pick<W, ACT, MODE, 3, true, false, LIN>())
-                      : ((a.L & 1) ? fwd_pick<W, ACT, MODE, 4, false, false, LIN>()
-                                   : fwd_pick<W, ACT, MODE, 3, false, false, LIN>());
+  if constexpr (MODE == FWD_INFER && W == 128 && XU == 1) {
+    // The unaligned loads need more registers than 16 waves leave.  Where 12
+    // waves cost more than they bring (streamed weights are staged once per
+    // tile of 384 instead of 512 rows: 7 matrices, in 63, 300001 rows 69 against
+    // 64 us; the even-matrix fused loop: 4 matrices, in 63, 2^20 rows 95 against
+    // 90), X is loaded one feature at a time.  Resident weights otherwise: in
+    // 39, out 108, 4 matrices, 284203 rows 42.2 -> 33.3 us; in 127, 5 matrices,
+    // 2^20 rows 158.7 -> 147.2.
+    if (!res) pk = fwd_pick<W, ACT, MODE, 0, false, false, LIN, false, 2>();
+    else if (a.L >= 2 && SO == 1)
+      pk = odd ? fwd_pick<W, ACT, MODE, 1, true, false, LIN, false, XU>()
+               : fwd_pick<W, ACT, MODE, 0, true, false, LIN, false, 2>();
+    else if (a.L >= 2)
+      pk = odd ? fwd_pick<W, ACT, MODE, 4, true, false, LIN, false, XU>()
+               : fwd_pick<W, ACT, MODE, 3, true, false, LIN, false, XU>();
+  } else if constexpr (MODE == FWD_INFER && W >= 64) {
+    if (res && a.L >= 2 && SO == 1)
+      pk = odd ? fwd_pick<W, ACT, MODE, 1, true, false, LIN, false, XU>()
+               : fwd_pick<W, ACT, MODE, 2, true, false, LIN, false, XU>();
+    else if (a.L >= 2)
+      pk = res ? (odd ? fwd_pick<W, ACT, MODE, 4, true, false, LIN, false, XU>()
+                      : fwd_pick<W, ACT, MODE, 3, true, false, LIN, false, XU>())
+               : (odd ? fwd_pick<W, ACT, MODE, 4, false, false, LIN, false, XU>()
+                      : fwd_pick<W, ACT, MODE, 3, false, false, LIN, false, XU>());
   }
   if constexpr (W <= 64) {
     // Small batches: fewer than two row tiles of the tile configuration
     // (NT NW 16 rows) per CU (widths up to 64, whose weights leave LDS for
     // several workgroups per CU), inference and training forward alike.
     const int64_t cfg_rows = (int64_t)TileCfg<W>::NT * TileCfg<W>::NW * 16;
-    if ((a.M + cfg_rows - 1) / cfg_rows <= 2 * (int64_t)di.cus && a.resident)
-      pk = fwd_pick<W, ACT, MODE, 0, true, true, LIN>();
+    if ((a.M + cfg_rows - 1) / cfg_rows <= 2 * (int64_t)di.cus && res)
+      pk = fwd_pick<W, ACT, MODE, 0, true, true, LIN, false, XU>();
   }
   a.ntiles = (int)((a.M + pk.rows - 1) / pk.rows);
   int occ = 0;
@@ -651,26 +656,33 @@ static hipError_t launch_t(const FwdArgs& a0, hipStream_t stream, int* grid_out)
   return hipGetLastError();
 }
 
-template <int W, int ACT>
+template <int W, int ACT, int XU>
 static hipError_t by_mode(int mode, const FwdArgs& a, hipStream_t s, int* g) {
   switch (mode) {
     case FWD_INFER:
-      return a.out_act == ACT_LINEAR ? launch_t<W, ACT, FWD_INFER, true>(a, s, g)
-                                     : launch_t<W, ACT, FWD_INFER, false>(a, s, g);
-    case FWD_STASH: return launch_t<W, ACT, FWD_STASH, false>(a, s, g);
+      return a.out_act == ACT_LINEAR ? launch_t<W, ACT, FWD_INFER, true, XU>(a, s, g)
+                                     : launch_t<W, ACT, FWD_INFER, false, XU>(a, s, g);
+    case FWD_STASH: return launch_t<W, ACT, FWD_STASH, false, XU>(a, s, g);
     default:
-      return a.out_act == ACT_LINEAR ? launch_t<W, ACT, FWD_TRAIN, true>(a, s, g)
-                                     : launch_t<W, ACT, FWD_TRAIN, false>(a, s, g);
+      return a.out_act == ACT_LINEAR ? launch_t<W, ACT, FWD_TRAIN, true, XU>(a, s, g)
+                                     : launch_t<W, ACT, FWD_TRAIN, false, XU>(a, s, g);
   }
+}
+// XU: X rows that are not whole 16-byte pieces are loaded unaligned.  Its own
+// kernel: both kinds of load in one held registers that width-128 inference
+// does not have.
+template <int W, int ACT>
+static hipError_t by_x(int mode, const FwdArgs& a, hipStream_t s, int* g) {
+  return (a.in_dim & 7) == 0 ? by_mode<W, ACT, 0>(mode, a, s, g) : by_mode<W, ACT, 1>(mode, a, s, g);
 }
 
 template <int W>
 static hipError_t by_act(int act, int mode, const FwdArgs& a, hipStream_t s, int* g) {
   switch (act) {
-    case ACT_RELU: return by_mode<W, ACT_RELU>(mode, a, s, g);
-    case ACT_SIGMOID: return by_mode<W, ACT_SIGMOID>(mode, a, s, g);
-    case ACT_SINE: return by_mode<W, ACT_SINE>(mode, a, s, g);
-    default: return by_mode<W, ACT_LINEAR>(mode, a, s, g);
+    case ACT_RELU: return by_x<W, ACT_RELU>(mode, a, s, g);
+    case ACT_SIGMOID: return by_x<W, ACT_SIGMOID>(mode, a, s, g);
+    case ACT_SINE: return by_x<W, ACT_SINE>(mode, a, s, g);
+    default: return by_x<W, ACT_LINEAR>(mode, a, s, g);
   }
 }
 

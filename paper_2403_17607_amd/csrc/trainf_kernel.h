@@ -120,18 +120,8 @@ __global__ __launch_bounds__(kTrainfWaves * 64) void trainf_kernel(const TrainfA
   // strips (lane (g, i): row i, columns 16 s + 4 g .. + 3).
   u32x4 xin[NT][KBW], tq[NT][OS];
   auto load_x = [&](const Rows& r, u32x4 (&dst)[NT][KBW]) {
-    if constexpr (VEC) {
-      const rsrc_t xr = make_rsrc(a.X + r.row0 * in_dim, r.vr * in_dim * 2);
-#pragma unroll
-      for (int kb = 0; kb < KBW; ++kb) {
-        const int f0 = kb * 32 + lg * 8;
-        const uint32_t voff = f0 < in_dim ? (uint32_t)((li * in_dim + f0) * 2) : kOOB;
-#pragma unroll
-        for (int n = 0; n < NT; ++n) dst[n][kb] = bload128(xr, voff, (uint32_t)(n * 32 * in_dim));
-      }
-    } else {
-      load_x_rows<NT, KBW>(a.X, r.row0, M, in_dim, li, lg, dst);
-    }
+    if constexpr (VEC) load_x_aligned<NT, KBW>(a.X, r.row0, M, in_dim, li, lg, dst);
+    else load_x_unaligned<NT, KBW>(a.X, r.row0, M, in_dim, li, lg, dst);
   };
   auto load_xt = [&](int tile) {
     const Rows r = rows_of(tile);
@@ -164,7 +154,7 @@ __global__ __launch_bounds__(kTrainfWaves * 64) void trainf_kernel(const TrainfA
 
     // ---- forward: hidden activations a_1 .. a_{L-1} kept as strips
     // (lane (g, i) of block n: row 16 n + i, features 16 s + 4 g .. + 3).
-    if constexpr (!VEC) mask_x_rows<NT, KBW>(in_dim, lg, xin);
+    if constexpr (!VEC) mask_x_rows<NT, KBW>(a.X, r.row0, M, in_dim, li, lg, xin);
     u32x2 st[L - 1][NT][SW];
     u32x2 cs[CSL][NT][SW];  // sine: bf16 cos of the pre-activations
     // k-block kb of layer l's input for block n, chain order
@@ -299,7 +289,7 @@ __global__ __launch_bounds__(kTrainfWaves * 64) void trainf_kernel(const TrainfA
       constexpr int l = decltype(lc)::value;
       constexpr int SD = Gm::sd(l), GO = Gm::goff(l);
       if constexpr (l == 0) {
-        if constexpr (!VEC) mask_x_strips<W, NT, KBW>(in_dim, lg, xs4);
+        if constexpr (!VEC) mask_x_strips<W, NT, KBW>(a.X, r.row0, M, in_dim, li, lg, xs4);
 #pragma unroll
         for (int n = 0; n < NT; ++n)
 #pragma unroll

@@ -179,18 +179,8 @@ __global__ __launch_bounds__(kTrainfWaves * 64) void trainw_kernel(const TrainfA
   // strips (lane (g, i): row 16 n + i, columns 16 s + 4 g .. + 3).
   u32x4 xin[NT][KBW], tq[NT][OS];
   auto load_x = [&](const Rows& r, u32x4 (&dst)[NT][KBW]) {
-    if constexpr (VEC) {
-      const rsrc_t xr = make_rsrc(a.X + r.row0 * in_dim, r.vr * in_dim * 2);
-#pragma unroll
-      for (int kb = 0; kb < KBW; ++kb) {
-        const int f0 = kb * 32 + lg * 8;
-        const uint32_t voff = f0 < in_dim ? (uint32_t)((li * in_dim + f0) * 2) : kOOB;
-#pragma unroll
-        for (int n = 0; n < NT; ++n) dst[n][kb] = bload128(xr, voff, (uint32_t)(n * 32 * in_dim));
-      }
-    } else {
-      load_x_rows<NT, KBW>(a.X, r.row0, M, in_dim, li, lg, dst);
-    }
+    if constexpr (VEC) load_x_aligned<NT, KBW>(a.X, r.row0, M, in_dim, li, lg, dst);
+    else load_x_unaligned<NT, KBW>(a.X, r.row0, M, in_dim, li, lg, dst);
   };
   auto load_xt = [&](int tile) {
     const Rows r = rows_of(tile);
@@ -223,7 +213,7 @@ __global__ __launch_bounds__(kTrainfWaves * 64) void trainw_kernel(const TrainfA
     // ---- forward: a_1 .. a_{L-1} of the wave's rows in chain order (the
     // next layer's B operand; k-block kb holds strips 2 kb and 2 kb + 1).
     u32x4 ach[L - 1][NT][KBW];
-    if constexpr (!VEC) mask_x_rows<NT, KBW>(in_dim, lg, xin);
+    if constexpr (!VEC) mask_x_rows<NT, KBW>(a.X, r.row0, M, in_dim, li, lg, xin);
     u32x4 cch[CSL][NT][KBW];  // sine: bf16 cos of the pre-activations, same order
     static_for<0, L - 1>([&](auto lc) {
       constexpr int l = decltype(lc)::value;
@@ -359,7 +349,7 @@ __global__ __launch_bounds__(kTrainfWaves * 64) void trainw_kernel(const TrainfA
         load_x(r, xc);
         if constexpr (L < 5) load_xt(tile + G);
       }
-      if constexpr (!VEC && l == 0) mask_x_rows<NT, KBW>(in_dim, lg, xc);
+      if constexpr (!VEC && l == 0) mask_x_rows<NT, KBW>(a.X, r.row0, M, in_dim, li, lg, xc);
       if constexpr (NT == 2) {
         static_for<0, SD>([&](auto sc) {
           constexpr int s = decltype(sc)::value;
