@@ -10,9 +10,8 @@
 //
 // A workgroup of eight waves owns a tile of 128 batch rows at a time
 // (persistent loop over tiles).  Each wave carries the deltas of its own 16
-// rows through the layers in VGPRs exactly as the unfused backward kernel
-// does: chain order, backward-packed weights resident in LDS as the MFMA A
-// operand, ReLU masks from the forward pass.
+// rows through the layers in VGPRs (chain order, backward-packed weights
+// resident in LDS as the MFMA A operand, ReLU masks from the forward pass).
 //
 // G_i is a contraction over the batch, so its MFMA operands need each lane
 // to hold batch rows of one feature, the transpose of the delta layout.
