@@ -172,10 +172,13 @@ int mlp_backward_dx(const mlp_t* h, const void* packed, const uint16_t* X,
  * accumulates the weight gradients without storing the deltas (the fusion
  * section V of the paper proposes); for other nets the same fusion in
  * segments of a few layers (up to 9, 7, 5 and 3 at widths 16, 32, 64 and
- * 128), one kernel each, with only the delta between two segments stored.
+ * 128), one kernel each, with only the delta between two segments stored;
+ * small batches of nets of several segments instead run one kernel that
+ * stores every delta and one that contracts them.
  * Then a fixed-order reduction, so G and the loss are bitwise the same from
  * run to run.  mlp_backward runs the width-128 fused kernel under the same
- * rule and otherwise, as mlp_backward_dx does for every net, the segments.
+ * rule and otherwise, as mlp_backward_dx does for every net, the segments or
+ * (small batches) the two kernels.
  */
 int mlp_train_step(const mlp_t* h, const void* packed, const uint16_t* X,
                    const float* T, uint16_t* Y, float* G, float* loss,

@@ -82,6 +82,7 @@ PackGeom pack_geom(const mlp* h) {
 struct WsLayout {
   int64_t M16;
   size_t stashA, stashS, reluMask, deltaH, deltaOut, cOut, partial, lossPart, total;
+  int P, chunks_per_block;  // gradient kernel: workgroups per layer, chunks each
 };
 
 WsLayout ws_layout(const mlp* h, int64_t M) {
@@ -98,15 +99,15 @@ WsLayout ws_layout(const mlp* h, int64_t M) {
   w.deltaH = o; o = round_up(o + hid, 256);
   w.deltaOut = o; o = round_up(o + (size_t)w.M16 * OP * 2, 256);
   w.cOut = o; o = round_up(o + (h->out_act != MLP_ACT_LINEAR ? (size_t)w.M16 * OP * 4 : 0), 256);
-  // Room for the partial sums of up to kPartialTarget / L workgroups of
-  // partial_rows rows or more each.
-  const int CH = partial_rows(W);
+  const int CH = wgrad_chunk(W);
   const int64_t nch = (M + CH - 1) / CH;
-  int64_t P = (kPartialTarget + L - 1) / L;
+  int64_t P = (kWgradTargetBlocks + L - 1) / L;
   if (P > nch) P = nch;
   if (P < 1) P = 1;
   const int64_t cpb = nch > 0 ? (nch + P - 1) / P : 0;
-  P = cpb > 0 ? (nch + cpb - 1) / cpb : 1;
+  P = cpb > 0 ? (nch + cpb - 1) / cpb : 1;  // no empty workgroups
+  w.P = (int)P;
+  w.chunks_per_block = (int)cpb;
   // The backward and one-kernel training kernels write one partial per
   // workgroup, at most one per 128 rows and at most kBwdgMaxBlocks.
   int64_t Pf = (M + kBwdgRows - 1) / kBwdgRows;
@@ -166,12 +167,15 @@ PackArgs pack_args(const mlp* h, const uint16_t* W, void* packed) {
   return a;
 }
 
-// Whether a backward pass of this net reads the ReLU mask words: only the
-// fused backward at width 128 (the others take relu' from the stashed
-// activations, which they read anyway).
-bool reads_masks(const mlp* h) {
-  return h->act == MLP_ACT_RELU &&
-         backward_fused_supported(h->width, n_mats(h), h->act, h->out_dim);
+bool fused_backward(const mlp* h) {
+  return backward_fused_supported(h->width, n_mats(h), h->act, h->out_dim);
+}
+
+// Whether a backward pass of M rows of this net may read the ReLU mask words:
+// the fused backward at width 128 and the delta kernel do (the segments take
+// relu' from the stashed activations, which they read anyway).
+bool reads_masks(const mlp* h, int64_t M) {
+  return h->act == MLP_ACT_RELU && (fused_backward(h) || backward_pair(h->width, n_mats(h), h->act, false, M));
 }
 
 // Fixed-order sum of P weight-gradient partials (and the loss partials).
@@ -221,13 +225,66 @@ int run_fused_backward(const mlp* h, const void* packed, const uint16_t* X, cons
   return run_reduce(h, w, ws, M, P, G, loss, nloss, s);
 }
 
-// The segmented backward pass of a net of any depth, seeded from dY or from the output delta the training forward wrote, with
-// the input gradient when dX is given; then the reduce.
-int run_bwds(const mlp* h, const void* packed, const uint16_t* X, const float* dY, float* dX, const WsLayout& w,
+// The delta and gradient kernel pair, seeded from dY or from the output delta
+// that the training forward wrote, with the input gradient when dX is given;
+// then the reduce.  For M that backward_pair covers, M > 0.
+int run_pair(const mlp* h, const void* packed, const uint16_t* X, const float* dY, float* dX, const WsLayout& w,
              uint8_t* ws, int64_t M, float* G, float* loss, int nloss, hipStream_t s) {
-  if (M <= 0) return run_reduce(h, w, ws, M, 0, G, loss, nloss, s);
   const PackGeom g = pack_geom(h);
+  const uint8_t* pk = static_cast<const uint8_t*>(packed);
+  BwdArgs b{};
+  b.packed = reinterpret_cast<const u32x4*>(pk + (size_t)g.fwd_total * 1024);
+  b.packed0 = reinterpret_cast<const u32x4*>(pk + (size_t)(g.fwd_total + g.bwd_total) * 1024);
+  b.stashA = reinterpret_cast<const uint16_t*>(ws + w.stashA);
+  b.stashS = h->act == MLP_ACT_SINE ? reinterpret_cast<const uint16_t*>(ws + w.stashS) : nullptr;
+  b.deltaH = reinterpret_cast<uint16_t*>(ws + w.deltaH);
+  b.deltaOut = reinterpret_cast<uint16_t*>(ws + w.deltaOut);
+  b.cOut = h->out_act != MLP_ACT_LINEAR ? reinterpret_cast<const float*>(ws + w.cOut) : nullptr;
+  b.dY = dY;
+  b.reluMask = h->act == MLP_ACT_RELU ? reinterpret_cast<const uint32_t*>(ws + w.reluMask) : nullptr;
+  b.dX = dX;
+  b.M = M;
+  b.M16 = w.M16;
+  b.in_dim = h->in_dim;
+  b.out_dim = h->out_dim;
+  b.L = n_mats(h);
+  b.out_act = h->out_act;
+  const int64_t rows = tile_rows(h->width);
+  b.ntiles = (int)((M + rows - 1) / rows);
+  b.layH_frags = g.bwd_hidden;
+  b.total_frags = g.bwd_total;
+  hipError_t e = launch_backward(h->width, h->act, dY != nullptr, b, s);
+  if (e != hipSuccess) return hip_fail(e, "delta kernel launch");
+  WgradArgs a{};
+  a.X = X;
+  a.stashA = b.stashA;
+  a.deltaH = b.deltaH;
+  a.deltaOut = b.deltaOut;
+  a.partial = reinterpret_cast<float*>(ws + w.partial);
+  a.M = M;
+  a.M16 = w.M16;
+  a.params = param_count(h);
+  a.in_dim = h->in_dim;
+  a.out_dim = h->out_dim;
+  a.L = b.L;
+  a.P = w.P;
+  a.chunks_per_block = w.chunks_per_block;
+  e = launch_wgrad(h->width, a, s);
+  if (e != hipSuccess) return hip_fail(e, "weight-gradient kernel launch");
+  return run_reduce(h, w, ws, M, w.P, G, loss, nloss, s);
+}
+
+// The segmented backward pass of a net of any depth, seeded from dY or from
+// the output delta that the training forward wrote, with the input gradient
+// when dX is given; then the reduce.  Small batches of deep nets run the pair
+// above instead.
+int run_backward(const mlp* h, const void* packed, const uint16_t* X, const float* dY, float* dX, const WsLayout& w,
+                 uint8_t* ws, int64_t M, float* G, float* loss, int nloss, hipStream_t s) {
+  if (M <= 0) return run_reduce(h, w, ws, M, 0, G, loss, nloss, s);
   const int L = n_mats(h);
+  if (backward_pair(h->width, L, h->act, dX != nullptr, M))
+    return run_pair(h, packed, X, dY, dX, w, ws, M, G, loss, nloss, s);
+  const PackGeom g = pack_geom(h);
   BwdsPlan p{};
   hipError_t e = bwds_plan(h->width, L, h->act, M, &p);
   if (e != hipSuccess) return hip_fail(e, "backward plan");
@@ -519,7 +576,7 @@ int mlp_forward(const mlp_t* h, const void* packed, const uint16_t* X, uint16_t*
     uint8_t* ws = static_cast<uint8_t*>(stash);
     a.stashA = reinterpret_cast<uint16_t*>(ws + w.stashA);
     a.stashS = h->act == MLP_ACT_SINE ? reinterpret_cast<uint16_t*>(ws + w.stashS) : nullptr;
-    a.reluMask = reads_masks(h) ? reinterpret_cast<uint32_t*>(ws + w.reluMask) : nullptr;
+    a.reluMask = reads_masks(h, M) ? reinterpret_cast<uint32_t*>(ws + w.reluMask) : nullptr;
     a.cOut = h->out_act != MLP_ACT_LINEAR ? reinterpret_cast<float*>(ws + w.cOut) : nullptr;
     mode = FWD_STASH;
   }
@@ -547,8 +604,9 @@ int mlp_backward_dx(const mlp_t* h, const void* packed, const uint16_t* X, const
   hipStream_t s = static_cast<hipStream_t>(stream);
   const WsLayout w = ws_layout(h, M);
   uint8_t* ws = static_cast<uint8_t*>(ws_);
-  if (!dX && M > 0 && reads_masks(h)) return run_fused_backward(h, packed, X, dY, w, ws, M, G, nullptr, 0, 1, false, s);
-  return run_bwds(h, packed, X, dY, dX, w, ws, M, G, nullptr, 0, s);
+  if (!dX && M > 0 && fused_backward(h))
+    return run_fused_backward(h, packed, X, dY, w, ws, M, G, nullptr, 0, 1, false, s);
+  return run_backward(h, packed, X, dY, dX, w, ws, M, G, nullptr, 0, s);
 }
 
 int mlp_train_step(const mlp_t* h, const void* packed, const uint16_t* X, const float* T,
@@ -625,8 +683,8 @@ int train_step_impl(const mlp_t* h, const void* packed, const uint16_t* X, const
     a.stashS = h->act == MLP_ACT_SINE ? reinterpret_cast<uint16_t*>(ws + w.stashS) : nullptr;
     // The fused backward at width 128 takes the activations transposed (the
     // forward has matrix-core time to spare, the backward does not).
-    const bool fused = reads_masks(h);
-    a.reluMask = fused ? reinterpret_cast<uint32_t*>(ws + w.reluMask) : nullptr;
+    const bool fused = fused_backward(h);
+    a.reluMask = reads_masks(h, M) ? reinterpret_cast<uint32_t*>(ws + w.reluMask) : nullptr;
     a.stash_t = fused ? 1 : 0;
     a.deltaOut = reinterpret_cast<uint16_t*>(ws + w.deltaOut);
     a.lossPart = reinterpret_cast<float*>(ws + w.lossPart);
@@ -634,7 +692,7 @@ int train_step_impl(const mlp_t* h, const void* packed, const uint16_t* X, const
     if (e != hipSuccess) return hip_fail(e, "forward kernel launch");
     if (fused) return run_fused_backward(h, packed, X, nullptr, w, ws, M, G, loss, nloss, 0, true, s);
   }
-  return run_bwds(h, packed, X, nullptr, nullptr, w, ws, M, G, loss, nloss, s);
+  return run_backward(h, packed, X, nullptr, nullptr, w, ws, M, G, loss, nloss, s);
 }
 
 }  // namespace

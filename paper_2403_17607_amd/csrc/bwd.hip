@@ -1,0 +1,43 @@
+// The delta and gradient kernel pair (bwd_kernel.h, wgrad.hip): when it is
+// used, and dispatch on the width; each width's instantiations are compiled in
+// their own translation unit (bwd16.hip .. bwd128.hip).
+#include "bwd_kernel.h"
+
+namespace ffmlp {
+
+// Small batches of nets of several segments.  Each segment of bwds_kernel.h is
+// a launch with some 3 us of its own (arguments, weights, first loads, the
+// write of its partial G) before and after a tile, where the delta kernel
+// walks all layers in one launch and the gradient kernel runs them side by
+// side; and at width 128 a segment net's partial G of every workgroup (1.1 MB at
+// 17 matrices) is more to reduce.  From some rows on, what the segments save
+// (every delta stored and read, every activation read again) is more.
+// Measured, backward and reduce of ReLU nets of 17 matrices, the segments' time
+// over the pair's:
+//   32 wide:  4096 rows 25 / 20 us, 32768 rows 0.97, 2^17 rows 0.58
+//   64 wide:  4096 rows 41 / 29 us, 60000 rows 0.98, 2^17 rows 0.74
+//   128 wide: 1024 rows 91 / 80 us, 32768 rows 1.26, 2^17 rows 0.93
+// Between, over 6 to 33 matrices, the crossing moves with the number of
+// segments and the activation (sigmoid's and sine's delta kernels read a value
+// where ReLU's reads a mask bit; dX adds as much to both): the lines below lie
+// where the two are within some 5%.
+bool backward_pair(int width, int L, int act, bool dx, int64_t M) {
+  const int n = bwds_segments(width, L);
+  const bool sine = act == ACT_SINE, sigmoid = act == ACT_SIGMOID;
+  if (width == 16) return n >= 3 && M <= (sine ? 24576 : (sigmoid ? 4096 : 8192) * (int64_t)(n - 1));
+  if (width == 32) return n >= 2 && M <= (n == 2 ? (sine ? 24576 : 8192) : (sigmoid ? 16384 : 32768));
+  if (width == 64) return n >= 2 && M <= (n == 2 ? 24576 : (n <= 4 ? 49152 : 40960));
+  return !sigmoid && n >= (sine ? 6 : (dx ? 5 : 4)) && M <= 16384 * (int64_t)(n < 8 ? n : 8);
+}
+
+hipError_t launch_backward(int width, int act, int seeded, const BwdArgs& a, hipStream_t s) {
+  switch (width) {
+    case 16: return launch_backward_w<16>(act, seeded, a, s);
+    case 32: return launch_backward_w<32>(act, seeded, a, s);
+    case 64: return launch_backward_w<64>(act, seeded, a, s);
+    case 128: return launch_backward_w<128>(act, seeded, a, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace ffmlp

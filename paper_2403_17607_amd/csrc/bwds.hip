@@ -6,15 +6,16 @@
 
 namespace ffmlp {
 
+int bwds_segments(int width, int L) { return (L + bwds_max(width) - 1) / bwds_max(width); }
+
 hipError_t bwds_plan(int width, int L, int act, int64_t M, BwdsPlan* out) {
   (void)act;
   DeviceInfo di;
   hipError_t e = device_info(&di);
   if (e != hipSuccess) return e;
-  const int most = bwds_max(width);
   const int64_t rows = kBwdsWaves * 16 * (width >= 64 ? 1 : 2);
   BwdsPlan p;
-  p.nseg = (L + most - 1) / most;
+  p.nseg = bwds_segments(width, L);
   p.base = L / p.nseg;
   p.rem = L % p.nseg;
   p.ntiles = (int)((M + rows - 1) / rows);

@@ -73,11 +73,28 @@ inline int tile_rows(int width) {
   }
 }
 
-// Rows per partial sum that the workspace size allows for (see ws_layout).
-inline int partial_rows(int width) { return 16384 / width; }
+// Weight-gradient kernel geometry: each wave owns a TBK x TBJ block of
+// 16x16 output tiles; GK x GJ blocks cover G; KS waves split every chunk of
+// the batch; each wave runs KSW 32-row contraction steps per chunk.
+template <int W> struct WgCfg;
+// The chunk is CH = 32 KS KSW rows, so CH * W / 8 = 2048 16-byte units per
+// tensor at every width (eight per thread, all in flight at once).
+template <> struct WgCfg<16> { static constexpr int TBK = 1, TBJ = 1, GK = 1, GJ = 1, KS = 4, KSW = 8; };
+template <> struct WgCfg<32> { static constexpr int TBK = 2, TBJ = 2, GK = 1, GJ = 1, KS = 4, KSW = 4; };
+template <> struct WgCfg<64> { static constexpr int TBK = 2, TBJ = 2, GK = 2, GJ = 2, KS = 1, KSW = 8; };
+template <> struct WgCfg<128> { static constexpr int TBK = 4, TBJ = 4, GK = 2, GJ = 2, KS = 1, KSW = 4; };
+template <int W> constexpr int wg_chunk() { return 32 * WgCfg<W>::KS * WgCfg<W>::KSW; }
+inline int wgrad_chunk(int width) {
+  switch (width) {
+    case 16: return wg_chunk<16>();
+    case 32: return wg_chunk<32>();
+    case 64: return wg_chunk<64>();
+    default: return wg_chunk<128>();
+  }
+}
 
 constexpr int kMaxLossParts = 4096;  // upper bound on forward workgroups
-constexpr int kPartialTarget = 1024;
+constexpr int kWgradTargetBlocks = 1024;
 
 struct FwdArgs {
   const u32x4* packed;  // forward-packed weights, all layers
@@ -97,6 +114,34 @@ struct FwdArgs {
   uint32_t lay0_frags, layH_frags, total_frags;  // 1 KiB fragment counts
   int stash_t;          // training forward at width 128 for the fused backward:
                         // stashA holds each strip transposed (see fwd_kernel.h)
+};
+
+// Delta kernel (bwd_kernel) and gradient kernel (wgrad_kernel).
+struct BwdArgs {
+  const u32x4* packed;  // backward-packed weights, layers 1 .. L-1
+  const uint16_t* stashA;
+  const uint16_t* stashS;
+  uint16_t* deltaH;     // (L-1) x [M16][W]: delta_0 .. delta_{L-2}
+  uint16_t* deltaOut;   // [M16][OP]: delta_{L-1}
+  const float* cOut;    // [M16][OP] fp32 (seeded mode, nonlinear output)
+  const float* dY;      // [M][out_dim] (seeded mode)
+  const uint32_t* reluMask;  // (L-1) x [M16/16][64] ReLU mask words (ReLU nets)
+  const u32x4* packed0;  // backward-packed layer 0 (input gradient), read from global
+  float* dX;             // [M][in_dim] input gradient, or null
+  int64_t M, M16;
+  int in_dim, out_dim, L, out_act;
+  int ntiles, resident;
+  uint32_t layH_frags, total_frags;
+};
+struct WgradArgs {
+  const uint16_t* X;
+  const uint16_t* stashA;
+  const uint16_t* deltaH;
+  const uint16_t* deltaOut;
+  float* partial;       // [P][param_count]
+  int64_t M, M16, params;
+  int in_dim, out_dim, L;
+  int P, chunks_per_block;
 };
 
 // Fused backward pass with the weight gradients (bwdg_kernel): the deltas
@@ -209,6 +254,10 @@ struct OptArgs {
 // Host-side launchers (one per translation unit).  They return a HIP error.
 hipError_t launch_forward(int width, int act, int mode, const FwdArgs& a,
                           hipStream_t s, int* grid_out);
+hipError_t launch_backward(int width, int act, int seeded, const BwdArgs& a, hipStream_t s);
+hipError_t launch_wgrad(int width, const WgradArgs& a, hipStream_t s);
+// Whether a batch of M rows runs these two (dx: with the input gradient).
+bool backward_pair(int width, int L, int act, bool dx, int64_t M);
 // Fused backward pass and weight-gradient partials at width 128; *grid_out
 // receives the number of partials written.
 hipError_t launch_backward_fused(int L, int seeded, const BwdgArgs& a, hipStream_t s, int* grid_out);
@@ -223,6 +272,8 @@ bool train_fused_supported(int width, int L);
 // The segmented backward pass of one segment (a.hi .. a.lo), and the plan
 // of a whole net for M rows on the current device.
 hipError_t launch_bwds(int width, const BwdsArgs& a, hipStream_t s);
+// Number of segments of a net of L matrices.
+int bwds_segments(int width, int L);
 hipError_t bwds_plan(int width, int L, int act, int64_t M, BwdsPlan* out);
 hipError_t launch_reduce(const ReduceArgs& a, hipStream_t s);
 hipError_t launch_pack(const PackArgs& a, hipStream_t s);
