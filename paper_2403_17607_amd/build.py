@@ -18,7 +18,8 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libffmlp.so")
-SOURCES = ["api.hip", "fwd.hip", "fwd16.hip", "fwd32.hip", "fwd64.hip", "fwd128.hip", "bwdg128.hip",
+SOURCES = ["api.hip", "fwd.hip", "fwd16.hip", "fwd32.hip", "fwd64.hip", "fwd128.hip", 
+           "bwdg.hip", "bwdg64.hip", "bwdg128.hip",
            "bwd.hip", "bwd16.hip", "bwd32.hip", "bwd64.hip", "bwd128.hip", "wgrad.hip",
            "bwds.hip", "bwds16.hip", "bwds32.hip", "bwds64.hip", "bwds128.hip",
            "trainf.hip", "trainf16.hip", "trainf32.hip", "trainf64.hip", "reduce.hip", "optim.hip"]

@@ -167,15 +167,16 @@ PackArgs pack_args(const mlp* h, const uint16_t* W, void* packed) {
   return a;
 }
 
-bool fused_backward(const mlp* h) {
-  return backward_fused_supported(h->width, n_mats(h), h->act, h->out_dim);
+bool fused_backward(const mlp* h, bool seeded, int64_t M) {
+  return backward_fused_supported(h->width, n_mats(h), h->act, h->in_dim, h->out_dim, seeded, M);
 }
 
 // Whether a backward pass of M rows of this net may read the ReLU mask words:
 // the fused backward at width 128 and the delta kernel do (the segments take
 // relu' from the stashed activations, which they read anyway).
 bool reads_masks(const mlp* h, int64_t M) {
-  return h->act == MLP_ACT_RELU && (fused_backward(h) || backward_pair(h->width, n_mats(h), h->act, false, M));
+  return h->act == MLP_ACT_RELU && ((h->width == 128 && fused_backward(h, true, M)) ||
+                                    backward_pair(h->width, n_mats(h), h->act, false, M));
 }
 
 // Fixed-order sum of P weight-gradient partials (and the loss partials).
@@ -206,6 +207,7 @@ int run_fused_backward(const mlp* h, const void* packed, const uint16_t* X, cons
   a.X = X;
   a.stashA = reinterpret_cast<const uint16_t*>(ws + w.stashA);
   a.reluMask = reinterpret_cast<const uint32_t*>(ws + w.reluMask);
+  a.stashS = h->act == MLP_ACT_SINE ? reinterpret_cast<const uint16_t*>(ws + w.stashS) : nullptr;
   a.deltaOut = reinterpret_cast<const uint16_t*>(ws + w.deltaOut);
   a.cOut = h->out_act != MLP_ACT_LINEAR ? reinterpret_cast<const float*>(ws + w.cOut) : nullptr;
   a.dY = dY;
@@ -215,12 +217,13 @@ int run_fused_backward(const mlp* h, const void* packed, const uint16_t* X, cons
   a.params = param_count(h);
   a.in_dim = h->in_dim;
   a.out_dim = h->out_dim;
+  a.act = h->act;
   a.out_act = h->out_act;
   a.ntiles = (int)((M + kBwdgRows - 1) / kBwdgRows);
   a.layH_frags = g.bwd_hidden;
   a.stash_t = stash_t ? 1 : 0;
   int P = 0;
-  hipError_t e = launch_backward_fused(n_mats(h), seeded, a, s, &P);
+  hipError_t e = launch_backward_fused(h->width, n_mats(h), h->out_dim, seeded, a, s, &P);
   if (e != hipSuccess) return hip_fail(e, "fused backward kernel launch");
   return run_reduce(h, w, ws, M, P, G, loss, nloss, s);
 }
@@ -604,7 +607,7 @@ int mlp_backward_dx(const mlp_t* h, const void* packed, const uint16_t* X, const
   hipStream_t s = static_cast<hipStream_t>(stream);
   const WsLayout w = ws_layout(h, M);
   uint8_t* ws = static_cast<uint8_t*>(ws_);
-  if (!dX && M > 0 && fused_backward(h))
+  if (!dX && M > 0 && fused_backward(h, true, M))
     return run_fused_backward(h, packed, X, dY, w, ws, M, G, nullptr, 0, 1, false, s);
   return run_backward(h, packed, X, dY, dX, w, ws, M, G, nullptr, 0, s);
 }
@@ -683,7 +686,7 @@ int train_step_impl(const mlp_t* h, const void* packed, const uint16_t* X, const
     a.stashS = h->act == MLP_ACT_SINE ? reinterpret_cast<uint16_t*>(ws + w.stashS) : nullptr;
     // The fused backward at width 128 takes the activations transposed (the
     // forward has matrix-core time to spare, the backward does not).
-    const bool fused = fused_backward(h);
+    const bool fused = fused_backward(h, false, M);
     a.reluMask = reads_masks(h, M) ? reinterpret_cast<uint32_t*>(ws + w.reluMask) : nullptr;
     a.stash_t = fused ? 1 : 0;
     a.deltaOut = reinterpret_cast<uint16_t*>(ws + w.deltaOut);

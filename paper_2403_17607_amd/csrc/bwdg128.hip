@@ -1,15 +1,14 @@
-// Fused backward kernel for width 128: which nets it covers, and its
-// instantiations (the kernel is in bwdg_kernel.h).
+// Fused backward kernel instantiations for width 128 (the kernel is in
+// bwdg_kernel.h).
 #include "bwdg_kernel.h"
 
 namespace ffmlp {
 
-bool backward_fused_supported(int width, int L, int act, int out_dim) {
-  return width == 128 && L >= 2 && L <= kBwdgMaxL && act == ACT_RELU && out_dim <= 16;  // register budget
-}
-
-hipError_t launch_backward_fused(int L, int seeded, const BwdgArgs& a, hipStream_t s, int* grid_out) {
-  return bwdg_by_l<128, 1>(L, seeded, a, s, grid_out);
+template <>
+hipError_t launch_backward_fused_w<128>(int L, int out_dim, int seeded, const BwdgArgs& a, hipStream_t s,
+                                        int* grid_out) {
+  if (out_dim > 16) return hipErrorNotSupported;
+  return seeded ? bwdg_by_l<128, 1, 1, 0>(L, a, s, grid_out) : bwdg_by_l<128, 1, 0, 0>(L, a, s, grid_out);
 }
 
 }  // namespace ffmlp

@@ -4,14 +4,19 @@
 // paper computes G outside its fused kernel and names fusing it into the
 // backward pass as future work in section V).
 //
-// The hidden activations' derivative comes from the ReLU mask words the
-// forward pass wrote: the kernel covers the ReLU nets of width 128 with one
-// output strip whose whole G fits one workgroup's registers.
+// It covers nets whose whole G fits one workgroup's registers: the ReLU nets
+// of width 128 with one output strip, and seeded passes of width 64 (see
+// backward_fused_supported in bwdg.hip).  The hidden activations' derivative
+// comes at width 128 from the ReLU mask words the forward pass wrote (DER 0),
+// at width 64 from the stash: [A > 0] for ReLU (DER 1) and A (1 - A) for
+// sigmoid (DER 2) from the stored bf16 A (the rows of A this CU reads for its
+// G slices anyway, so mostly cache hits), bf16 cos C for sine and 1 for linear
+// (DER 2).
 //
 // A workgroup of eight waves owns a tile of 128 batch rows at a time
 // (persistent loop over tiles).  Each wave carries the deltas of its own 16
 // rows through the layers in VGPRs (chain order, backward-packed weights
-// resident in LDS as the MFMA A operand, ReLU masks from the forward pass).
+// resident in LDS as the MFMA A operand).
 //
 // G_i is a contraction over the batch, so its MFMA operands need each lane
 // to hold batch rows of one feature, the transpose of the delta layout.
@@ -76,7 +81,7 @@ struct BwdgGeom {
 // TST: stashA written transposed by the training forward (each 16-row
 // block's strip s as lane (g, n) = feature 16 s + n of rows 4 g .. 4 g + 3),
 // so the A operand of G_l is loaded as it is, with no transposes here.
-template <int W, int L, int OS, int SEEDED, bool XT8, bool TST = false>
+template <int W, int L, int OS, int SEEDED, int DER, bool XT8, bool TST = false>
 __global__ __launch_bounds__(kBwdgWaves * 64) void bwdg_kernel(const BwdgArgs a) {
   using Gm = BwdgGeom<W, L, OS, XT8>;
   constexpr int NW = Gm::NW, SW = Gm::SW, KBW = Gm::KBW, KBO = Gm::KBO, LDT = Gm::LDT;
@@ -89,7 +94,7 @@ __global__ __launch_bounds__(kBwdgWaves * 64) void bwdg_kernel(const BwdgArgs a)
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform
   const int li = lane & 15, lg = lane >> 4;
   const int64_t M = a.M;
-  const int in_dim = a.in_dim, out_dim = a.out_dim, out_act = a.out_act;
+  const int in_dim = a.in_dim, out_dim = a.out_dim, act = a.act, out_act = a.out_act;
   const bool xvec = (in_dim & 3) == 0;
   const int SO = (out_dim + 15) >> 4;  // strips of the output (at most OS)
   const int OP = SO * 16;
@@ -253,11 +258,31 @@ __global__ __launch_bounds__(kBwdgWaves * 64) void bwdg_kernel(const BwdgArgs a)
                                 t.vblk ? 256 : 0);
     return bload32(mr, lane * 4, 0u);
   };
+  // DER = 1: the derivative source of hidden activation idx (stash index),
+  // the wave's own 16 rows, all strips (none for linear layers).
+  auto load_der = [&](int idx, const TileGeom& t, u32x2 (&sv)[SW]) {
+    if (act == ACT_LINEAR) return;
+    const uint16_t* src = act == ACT_SINE ? a.stashS : a.stashA;
+    const rsrc_t r = make_rsrc(src + (size_t)idx * a.M16 * W + (size_t)t.row0 * W,
+                               (int64_t)t.vblk * 32 * W);
+#pragma unroll
+    for (int s = 0; s < SW; ++s) sv[s] = bload64(r, lane * 8, (uint32_t)(s * 512));
+  };
+  // The derivative of the hidden activation from its source value (DER 2):
+  // sigmoid a (1 - a) of the stored bf16 a, sine the stored bf16 cos c,
+  // linear 1.
+  auto der = [&](uint32_t half) -> float {
+    const float v = __uint_as_float(half);
+    return act == ACT_SIGMOID ? v * (1.f - v) : (act == ACT_SINE ? v : 1.f);
+  };
   // What a tile needs first, requested one tile ahead (during the previous
   // tile's last layer): the output delta (training mode), the mask words of
   // a_{L-1} and the A strip of layer L-1.
   u32x2 dq[OS];
   uint32_t mq = 0u;
+  u32x2 svq[DER ? SW : 1], sv[DER ? SW : 1];  // derivative sources (DER 1, 2)
+#pragma unroll
+  for (int s = 0; s < (DER ? SW : 1); ++s) svq[s] = sv[s] = u32x2{0u, 0u};
   auto fetch = [&](int tile) {
     const TileGeom t = geom(tile);
     if constexpr (!SEEDED) {
@@ -266,7 +291,8 @@ __global__ __launch_bounds__(kBwdgWaves * 64) void bwdg_kernel(const BwdgArgs a)
       for (int s = 0; s < OS; ++s)
         dq[s] = bload64(dr, lane * 8, s < SO ? (uint32_t)(s * 512) : kOOB);
     }
-    mq = load_mask(L - 2, t);
+    if constexpr (DER == 0) mq = load_mask(L - 2, t);
+    else load_der(L - 2, t, svq);
     load_a(std::integral_constant<int, L - 1>{}, t);
   };
 
@@ -327,6 +353,10 @@ __global__ __launch_bounds__(kBwdgWaves * 64) void bwdg_kernel(const BwdgArgs a)
       });
     }
     uint32_t mw = mq;  // relu'(a_{L-1})
+    if constexpr (DER != 0) {
+#pragma unroll
+      for (int s = 0; s < SW; ++s) sv[s] = svq[s];
+    }
 
     // Layer l.  Phase 1: D_{l+1} (in `cur`) transposed into DT.  Phase 2
     // (after a barrier): the wave's slice of G_l = A_l^T D_{l+1} over the
@@ -427,10 +457,21 @@ __global__ __launch_bounds__(kBwdgWaves * 64) void bwdg_kernel(const BwdgArgs a)
           f32x4 acc = zero4;
 #pragma unroll
           for (int kb = 0; kb < KBL; ++kb) acc = mfma16(af[kb], cur[kb], acc);
-          // relu'(a) is [a > 0]: zero the rounded products where a is 0
-          const uint32_t tm = mw >> (2 * s);
-          const uint32_t p0 = mask_halves(pack_bf16x2(acc[0], acc[1]), tm & 0x00010001u);
-          const uint32_t p1 = mask_halves(pack_bf16x2(acc[2], acc[3]), (tm >> 1) & 0x00010001u);
+          uint32_t p0, p1;
+          if constexpr (DER == 0) {
+            // relu'(a) is [a > 0]: zero the rounded products where a is 0
+            const uint32_t tm = mw >> (2 * s);
+            p0 = mask_halves(pack_bf16x2(acc[0], acc[1]), tm & 0x00010001u);
+            p1 = mask_halves(pack_bf16x2(acc[2], acc[3]), (tm >> 1) & 0x00010001u);
+          } else if constexpr (DER == 1) {
+            // ReLU from the stored activations: each bf16 half of a is >= 0,
+            // so its 0/1 multiplier is min(a, 1) as an unsigned 16-bit value
+            p0 = mask_halves(pack_bf16x2(acc[0], acc[1]), nonzero_halves(sv[s].x));
+            p1 = mask_halves(pack_bf16x2(acc[2], acc[3]), nonzero_halves(sv[s].y));
+          } else {
+            p0 = pack_bf16x2(acc[0] * der(sv[s].x << 16), acc[1] * der(sv[s].x & 0xffff0000u));
+            p1 = pack_bf16x2(acc[2] * der(sv[s].y << 16), acc[3] * der(sv[s].y & 0xffff0000u));
+          }
           if constexpr (s & 1) {
             nxt[s >> 1].z = p0;
             nxt[s >> 1].w = p1;
@@ -441,7 +482,10 @@ __global__ __launch_bounds__(kBwdgWaves * 64) void bwdg_kernel(const BwdgArgs a)
         }
         __builtin_amdgcn_sched_barrier(0);
       });
-      if constexpr (l >= 2) mw = load_mask(l - 2, t);
+      if constexpr (l >= 2) {
+        if constexpr (DER == 0) mw = load_mask(l - 2, t);
+        else load_der(l - 2, t, sv);
+      }
       __syncthreads();  // every wave is done reading DT (and XT)
       if constexpr (Gm::XT_REUSE && l == 0) {
         // XT's space back to layer 1's weights for the next tile (waited
@@ -481,7 +525,7 @@ __global__ __launch_bounds__(kBwdgWaves * 64) void bwdg_kernel(const BwdgArgs a)
   });
 }
 
-template <int W, int L, int OS, int SEEDED, bool XT8, bool TST = false>
+template <int W, int L, int OS, int SEEDED, int DER, bool XT8, bool TST = false>
 static hipError_t bwdg_launch_t1(const BwdgArgs& a, hipStream_t stream, int* grid_out) {
   using Gm = BwdgGeom<W, L, OS, XT8>;
   DeviceInfo di;
@@ -489,7 +533,7 @@ static hipError_t bwdg_launch_t1(const BwdgArgs& a, hipStream_t stream, int* gri
   if (e != hipSuccess) return e;
   const size_t lds = Gm::lds_bytes();
   if (lds > (size_t)di.max_lds) return hipErrorNotSupported;
-  auto kern = bwdg_kernel<W, L, OS, SEEDED, XT8, TST>;
+  auto kern = bwdg_kernel<W, L, OS, SEEDED, DER, XT8, TST>;
   int occ = 0;
   e = kernel_occupancy(reinterpret_cast<const void*>(kern), kBwdgWaves * 64, lds, &occ);
   if (e != hipSuccess) return e;
@@ -503,29 +547,33 @@ static hipError_t bwdg_launch_t1(const BwdgArgs& a, hipStream_t stream, int* gri
 }
 
 // XT8: the X tile exchanged through LDS for G_0 (in_dim a multiple of 8).
-template <int W, int L, int OS, int SEEDED>
+template <int W, int L, int OS, int SEEDED, int DER>
 static hipError_t bwdg_launch_t(const BwdgArgs& a, hipStream_t stream, int* grid_out) {
   if (a.stash_t) {
     // the transposed stash exists only for the training step at width 128
-    if constexpr (SEEDED == 0) {
-      if (a.in_dim % 8 == 0) return bwdg_launch_t1<W, L, OS, SEEDED, true, true>(a, stream, grid_out);
-      return bwdg_launch_t1<W, L, OS, SEEDED, false, true>(a, stream, grid_out);
+    if constexpr (W == 128 && SEEDED == 0) {
+      if (a.in_dim % 8 == 0) return bwdg_launch_t1<W, L, OS, SEEDED, DER, true, true>(a, stream, grid_out);
+      return bwdg_launch_t1<W, L, OS, SEEDED, DER, false, true>(a, stream, grid_out);
     }
     return hipErrorInvalidValue;
   }
-  if (a.in_dim % 8 == 0) return bwdg_launch_t1<W, L, OS, SEEDED, true>(a, stream, grid_out);
-  return bwdg_launch_t1<W, L, OS, SEEDED, false>(a, stream, grid_out);
+  if (a.in_dim % 8 == 0) return bwdg_launch_t1<W, L, OS, SEEDED, DER, true>(a, stream, grid_out);
+  if constexpr (W == 128) return bwdg_launch_t1<W, L, OS, SEEDED, DER, false>(a, stream, grid_out);
+  return hipErrorInvalidValue;  // width 64: multiples of 8 only
 }
 
-template <int W, int OS>
-static hipError_t bwdg_by_l(int L, int seeded, const BwdgArgs& a, hipStream_t s, int* g) {
+template <int W, int OS, int SEEDED, int DER>
+static hipError_t bwdg_by_l(int L, const BwdgArgs& a, hipStream_t s, int* g) {
   switch (L) {
-    case 2: return seeded ? bwdg_launch_t<W, 2, OS, 1>(a, s, g) : bwdg_launch_t<W, 2, OS, 0>(a, s, g);
-    case 3: return seeded ? bwdg_launch_t<W, 3, OS, 1>(a, s, g) : bwdg_launch_t<W, 3, OS, 0>(a, s, g);
-    case 4: return seeded ? bwdg_launch_t<W, 4, OS, 1>(a, s, g) : bwdg_launch_t<W, 4, OS, 0>(a, s, g);
-    case 5: return seeded ? bwdg_launch_t<W, 5, OS, 1>(a, s, g) : bwdg_launch_t<W, 5, OS, 0>(a, s, g);
+    case 2: return bwdg_launch_t<W, 2, OS, SEEDED, DER>(a, s, g);
+    case 3: return bwdg_launch_t<W, 3, OS, SEEDED, DER>(a, s, g);
+    case 4: return bwdg_launch_t<W, 4, OS, SEEDED, DER>(a, s, g);
+    case 5: return bwdg_launch_t<W, 5, OS, SEEDED, DER>(a, s, g);
     default: return hipErrorNotSupported;
   }
 }
+
+template <int W>
+hipError_t launch_backward_fused_w(int L, int out_dim, int seeded, const BwdgArgs& a, hipStream_t s, int* grid_out);
 
 }  // namespace ffmlp

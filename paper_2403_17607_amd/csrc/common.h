@@ -155,13 +155,14 @@ struct BwdgArgs {
   const u32x4* packed;       // backward-packed weights, layers 1 .. L-1
   const uint16_t* X;         // [M][in_dim]
   const uint16_t* stashA;    // (L-1) x [M16][W] tile images: a_1 .. a_{L-1}
-  const uint32_t* reluMask;  // (L-1) x [M16/16][64] ReLU mask words (ReLU nets)
+  const uint32_t* reluMask;  // (L-1) x [M16/16][64] ReLU mask words (width 128)
+  const uint16_t* stashS;    // (L-1) x [M16][W] bf16 cos of sine layers, or null
   const uint16_t* deltaOut;  // [M16][OP] output delta (training step)
   const float* cOut;         // [M16][OP] fp32 pre-activation (seeded, nonlinear output)
   const float* dY;           // [M][out_dim] (seeded mode)
   float* partial;            // [gridDim.x][params]
   int64_t M, M16, params;
-  int in_dim, out_dim, out_act;
+  int in_dim, out_dim, act, out_act;
   int ntiles;                // kBwdgRows-row tiles
   uint32_t layH_frags;       // 1 KiB fragments of one packed hidden layer
   int stash_t;               // stashA written transposed (FwdArgs::stash_t)
@@ -258,11 +259,13 @@ hipError_t launch_backward(int width, int act, int seeded, const BwdArgs& a, hip
 hipError_t launch_wgrad(int width, const WgradArgs& a, hipStream_t s);
 // Whether a batch of M rows runs these two (dx: with the input gradient).
 bool backward_pair(int width, int L, int act, bool dx, int64_t M);
-// Fused backward pass and weight-gradient partials at width 128; *grid_out
-// receives the number of partials written.
-hipError_t launch_backward_fused(int L, int seeded, const BwdgArgs& a, hipStream_t s, int* grid_out);
-// Whether launch_backward_fused covers a net (host-side shape check only).
-bool backward_fused_supported(int width, int L, int act, int out_dim);
+// Fused backward pass and weight-gradient partials; *grid_out receives the
+// number of partials written.
+hipError_t launch_backward_fused(int width, int L, int out_dim, int seeded, const BwdgArgs& a, hipStream_t s,
+                                 int* grid_out);
+// Whether a backward pass of M rows without the input gradient runs it
+// (host-side check only); at width 128 whatever `seeded` and M are.
+bool backward_fused_supported(int width, int L, int act, int in_dim, int out_dim, bool seeded, int64_t M);
 // Fused training step; *grid_out receives the number of G and loss
 // partials written.  hipErrorNotSupported when it does not cover the net.
 hipError_t launch_train_fused(int width, int L, int act, int out_dim, const TrainfArgs& a,

@@ -614,6 +614,30 @@ def test_fused_backward_shapes(ffmlp, gpu, width, depth, in_dim, out_dim, act, o
     log("  seeded grad errs", ["%.2e" % e for e in errs])
 
 
+@pytest.mark.parametrize("depth", [1, 2, 3, 4])
+@pytest.mark.parametrize("in_dim,out_dim,act,out_act,M", [
+    (8, 1, "relu", "sine", 1), (64, 64, "relu", "linear", 33000), (40, 17, "sine", "linear", 129),
+    (64, 16, "sigmoid", "relu", 34001), (24, 33, "linear", "sigmoid", 4000), (64, 16, "sine", "linear", 65536),
+    (64, 16, "sine", "linear", 65537), (16, 3, "relu", "linear", 131072), (16, 3, "relu", "linear", 131073)])
+def test_seeded_width_64(ffmlp, gpu, depth, in_dim, out_dim, act, out_act, M):
+    """Seeded passes of 2 to 5 matrices at width 64 and whole 16-byte X rows
+    run the fused kernel (bwdg_kernel): every derivative source, one output
+    strip and several, one row, ragged tiles and several per workgroup, and the
+    two sides of the batch size where the segments take over; G against the
+    segments' (backward_dx) and the oracle's, and bitwise the same again."""
+    W, X, _ = inputs(42, 64, depth, in_dim, out_dim, M)
+    dY = datagen.uniform(42, datagen.STREAM_AUX, (M, out_dim))
+    net = ffmlp.FusedMLP(64, depth, in_dim, out_dim, act, out_act)
+    onet = oracle_net(64, depth, in_dim, out_dim, act, out_act)
+    packed, ws, Xd, dYd = net.pack(W.to(gpu)), net.workspace(M, gpu), X.to(gpu), dY.to(gpu)
+    net.forward(packed, Xd, stash=ws)
+    G = net.backward(packed, Xd, dYd, ws)
+    assert torch.equal(net.backward(packed, Xd, dYd, ws), G)
+    Gs, _ = net.backward_dx(packed, Xd, dYd, ws)
+    check_grads(f64(G), onet.backward(W, X, dY), onet)
+    assert ((G - Gs).norm() / Gs.norm().clamp_min(1e-30)).item() < 1e-5
+
+
 @pytest.mark.parametrize("width,depth,in_dim,out_dim,act,out_act,M", [
     (16, 1, 5, 3, "sine", "sigmoid", 1), (16, 4, 16, 16, "relu", "linear", 257),
     (16, 3, 12, 7, "sigmoid", "relu", 4099),
