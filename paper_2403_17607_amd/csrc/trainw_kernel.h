@@ -57,17 +57,8 @@ struct TrainwGeom {
                 "width-64 fused training step");
 };
 
-// Two blocks per wave where the registers allow it: one output strip and no
-// cos source.  Measured at 2^20 rows: image-like net (in 32, 2 hidden layers,
-// sigmoid out 3) 110 -> 95 us, 5 matrices 181.5 -> 166 us.
-template <int L, int OS, int ACT, bool VEC>
-constexpr int trainw_nt() {
-  return (ACT != ACT_SINE && OS == 1) ? 2 : 1;
-}
-
-template <int L, int OS, int ACT, bool VEC>
+template <int L, int OS, int ACT, bool VEC, int NT>
 __global__ __launch_bounds__(kTrainfWaves * 64) void trainw_kernel(const TrainfArgs a) {
-  constexpr int NT = trainw_nt<L, OS, ACT, VEC>();
   using Gm = TrainwGeom<L, OS, NT>;
   constexpr int NW = Gm::NW, SW = Gm::SW, KBW = Gm::KBW, KBO = Gm::KBO, LDT = Gm::LDT, KS = Gm::KS;
   constexpr int NACC = Gm::nacc();
@@ -498,9 +489,9 @@ __global__ __launch_bounds__(kTrainfWaves * 64) void trainw_kernel(const TrainfA
   }
 }
 
-template <int L, int OS, int ACT, bool VEC>
-static hipError_t trainw_launch_t(const TrainfArgs& a0, hipStream_t stream, int* grid_out) {
-  using Gm = TrainwGeom<L, OS, trainw_nt<L, OS, ACT, VEC>()>;
+template <int L, int OS, int ACT, bool VEC, int NT>
+static hipError_t trainw_launch_nt(const TrainfArgs& a0, hipStream_t stream, int* grid_out) {
+  using Gm = TrainwGeom<L, OS, NT>;
   TrainfArgs a = a0;
   a.ntiles = (int)((a.M + Gm::ROWS - 1) / Gm::ROWS);
   if (a.fwd_total > (uint32_t)Gm::FF) return hipErrorInvalidValue;
@@ -509,7 +500,7 @@ static hipError_t trainw_launch_t(const TrainfArgs& a0, hipStream_t stream, int*
   if (e != hipSuccess) return e;
   const size_t lds = Gm::lds_bytes();
   if (lds > (size_t)di.max_lds) return hipErrorNotSupported;
-  auto kern = trainw_kernel<L, OS, ACT, VEC>;
+  auto kern = trainw_kernel<L, OS, ACT, VEC, NT>;
   int occ = 0;
   e = kernel_occupancy(reinterpret_cast<const void*>(kern), kTrainfWaves * 64, lds, &occ);
   if (e != hipSuccess) return e;
@@ -520,6 +511,22 @@ static hipError_t trainw_launch_t(const TrainfArgs& a0, hipStream_t stream, int*
   *grid_out = grid;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(kTrainfWaves * 64), lds, stream, a);
   return hipGetLastError();
+}
+
+// Two 16-row blocks per wave where the registers allow it (one output strip,
+// no cos source) and the batch has enough tiles: each LDS weight fragment feeds
+// two MFMAs, but a tile takes longer and there are half as many.  Measured at
+// 2^20 rows, one against two: image-like net (in 32, 2 hidden layers, sigmoid
+// out 3) 110 / 95 us, 5 matrices 181.5 / 166; 5 matrices, in 32, out 3: 4096 rows
+// 15.2 / 21.2, 24000 rows 0.85, 32768 rows 0.91, 36000 rows 1.19; in 64, out 16
+// 24000 rows equal, 32768 rows 1.07.
+constexpr int64_t kTrainwOneBlock = 24576;
+template <int L, int OS, int ACT, bool VEC>
+static hipError_t trainw_launch_t(const TrainfArgs& a, hipStream_t s, int* g) {
+  if constexpr (ACT != ACT_SINE && OS == 1) {
+    if (a.M > kTrainwOneBlock) return trainw_launch_nt<L, OS, ACT, VEC, 2>(a, s, g);
+  }
+  return trainw_launch_nt<L, OS, ACT, VEC, 1>(a, s, g);
 }
 
 template <int OS, int ACT, bool VEC>

@@ -645,6 +645,9 @@ def test_seeded_width_64(ffmlp, gpu, depth, in_dim, out_dim, act, out_act, M):
     (32, 4, 32, 20, "sine", "linear", 9000),
     (64, 1, 1, 1, "relu", "linear", 129), (64, 4, 64, 64, "sine", "linear", 3000),
     (64, 3, 12, 17, "sigmoid", "sigmoid", 700), (64, 2, 40, 16, "linear", "relu", 65541),
+    (64, 4, 63, 3, "relu", "linear", 24576), (64, 4, 63, 3, "relu", "linear", 24577),
+    (64, 3, 37, 7, "sigmoid", "sigmoid", 70001), (64, 1, 64, 16, "relu", "linear", 24577),
+    (64, 4, 37, 7, "relu", "linear", 131077),
 ])
 def test_one_kernel_step_shapes(ffmlp, gpu, width, depth, in_dim, out_dim, act, out_act, M):
     """The one-kernel training step (widths 16, 32, 64 with 2 to 5 matrices)
