@@ -48,11 +48,11 @@ def flops_per_row(width, depth, in_dim, out_dim):
 
 
 def fused_backward(width, depth, in_dim, out_dim, act):
-    """Whether the library's training step runs the fused backward kernel
-    (deltas kept on chip, weight gradients accumulated in the same kernel):
-    2 to 5 weight matrices and, at width 128, ReLU hidden layers and at most
-    16 outputs; otherwise it runs the three kernels (backward, weight
-    gradients, reduce).  The rule of include/ffmlp.h."""
+    """Whether a backward pass can keep every delta of the net on chip in one
+    kernel: 2 to 5 weight matrices and, at width 128, ReLU hidden layers and at
+    most 16 outputs.  The library's training step does so at width 128 (at
+    widths up to 64 it runs the whole step in one kernel, fused_step); the other
+    nets run in segments (segments) or, in small batches, in three kernels."""
     return 1 <= depth <= 4 and (width != 128 or (act == "relu" and out_dim <= 16))
 
 
@@ -63,8 +63,54 @@ def fused_step(width, depth):
     return width in (16, 32, 64) and 1 <= depth <= 4
 
 
+def segments(width, depth):
+    """Segments of the library's segmented backward pass: at most 9, 7, 5 and 3
+    matrices each at widths 16, 32, 64 and 128."""
+    return -(-(depth + 1) // {16: 9, 32: 7, 64: 5, 128: 3}[width])
+
+
+def three_kernels(width, depth, act, rows):
+    """Whether a training step of this batch runs the delta and gradient kernels
+    instead of the segments: small batches of nets of several segments, the
+    rule of backward_pair in csrc/bwd.hip."""
+    n = segments(width, depth)
+    if width == 16:
+        return n >= 3 and rows <= {"sine": 24576, "sigmoid": 4096 * (n - 1)}.get(act, 8192 * (n - 1))
+    if width == 32:
+        return n >= 2 and rows <= ((24576 if act == "sine" else 8192) if n == 2 else
+                                   (16384 if act == "sigmoid" else 32768))
+    if width == 64:
+        return n >= 2 and rows <= (24576 if n == 2 else 49152 if n <= 4 else 40960)
+    return act != "sigmoid" and n >= (6 if act == "sine" else 4) and rows <= 16384 * min(n, 8)
+
+
+def step_plan(width, depth, in_dim, out_dim, act, rows):
+    """What the library's training step runs: "one kernel", "fused", "segments"
+    or "three kernels"."""
+    if fused_step(width, depth):
+        return "one kernel"
+    if fused_backward(width, depth, in_dim, out_dim, act):
+        return "fused"
+    return "three kernels" if three_kernels(width, depth, act, rows) else "segments"
+
+
+def segmented_bytes_per_row(width, depth, in_dim, out_dim, act):
+    """HBM bytes per row of a training step in segments, without the partial
+    weight gradients: the forward reads X and T and writes the activations, the
+    output delta and (sine) the cos stash; the segments read X, the
+    activations, the output delta and the cos stash, and write and read the
+    delta between two of them."""
+    OP = (out_dim + 15) // 16 * 16
+    hid = depth * width * 2
+    cos = hid if act == "sine" else 0
+    return (2 * in_dim + 4 * out_dim + hid + 2 * OP + cos + 2 * in_dim + hid + 2 * OP + cos +
+            4 * width * (segments(width, depth) - 1))
+
+
 def train_bytes_per_row(width, depth, in_dim, out_dim, act, fused=None, masks=True):
-    """HBM bytes the training step must move per row.
+    """HBM bytes per row of the training step in one kernel, with the fused
+    backward, or (the other nets) in three kernels; segmented_bytes_per_row has
+    the nets that run in segments.
     One-kernel step (fused=None at widths 16, 32 and 64 with 2 to 5 matrices):
     X and T (the bench asks for no Y).
     Forward (both plans): reads X and T, writes the activations, the output
@@ -73,9 +119,7 @@ def train_bytes_per_row(width, depth, in_dim, out_dim, act, fused=None, masks=Tr
     activations (the weight-gradient operands; at widths up to 64 also the
     ReLU and sigmoid derivative source), plus the masks at width 128 and the
     cos stash of sine nets, and writes no deltas.
-    Three-kernel plan (an unfused backward; the library runs the other nets
-    in fused segments, which move less, and their rate is quoted against
-    this count all the same): the backward reads the output delta and the
+    Three-kernel plan: the backward reads the output delta and the
     derivative source of every hidden activation (ReLU: its mask, 16 B per
     row, or with masks=False the activation itself; sigmoid: the
     activation; sine: the stored cos; linear: nothing) and writes the hidden
@@ -103,6 +147,13 @@ def train_bytes_per_row(width, depth, in_dim, out_dim, act, fused=None, masks=Tr
     b += 2 * OP + deriv + hid                             # backward
     b += 2 * in_dim + hid + hid + 2 * OP                  # weight gradients
     return b
+
+
+def step_bytes_per_row(width, depth, in_dim, out_dim, act, rows):
+    """HBM bytes per row of the training step as the library runs it."""
+    if step_plan(width, depth, in_dim, out_dim, act, rows) == "segments":
+        return segmented_bytes_per_row(width, depth, in_dim, out_dim, act)
+    return train_bytes_per_row(width, depth, in_dim, out_dim, act)
 
 
 def measured_traffic(key):
@@ -251,7 +302,7 @@ def summarize(width, depth, in_dim, out_dim, M, act, out_act, m):
     fl_inf, fl_train = flops_per_row(width, depth, in_dim, out_dim)
     t_inf, t_train = m["infer_ms"], m["train_ms"]
     bytes_inf = 2 * in_dim + 2 * out_dim
-    bytes_train = train_bytes_per_row(width, depth, in_dim, out_dim, act)
+    bytes_train = step_bytes_per_row(width, depth, in_dim, out_dim, act, M)
     return {
         "infer": {"ms": t_inf, "samples_per_s": M / (t_inf * 1e-3),
                   "tflops": fl_inf * M / (t_inf * 1e-3) / 1e12,
@@ -355,7 +406,7 @@ def main():
     out_dim = args.out_dim
     m = measure(width, depth, in_dim, out_dim, M, args.act, args.out_act, K, Wm, R, args.inputs)
     d = summarize(width, depth, in_dim, out_dim, M, args.act, args.out_act, m)
-    fused = fused_backward(width, depth, in_dim, out_dim, args.act)
+    plan = step_plan(width, depth, in_dim, out_dim, args.act, M)
     fl_inf, _ = flops_per_row(width, depth, in_dim, out_dim)
     inf_tflops, train_gbs = d["infer"]["tflops"], d["train"]["hbm_gbs_algorithmic"]
     ms_per_step = m["ms_per_step"]
@@ -397,20 +448,21 @@ def main():
                                      "workload (profiles/traffic.json, scaled by a reference "
                                      "copy), null once the kernel's sources have changed",
                      "flops_per_row": fl_inf, "rows_per_launch": M},
-        "roofline_train": {"kernels": (("trainw_kernel" if width == 64 else "trainf_kernel") +
-                                       " (the whole step) + reduce_kernel"
-                                       if fused_step(width, depth) else
-                                       ("fwd_kernel (train) + " +
-                                        "bwdg_kernel (fused backward and weight gradients) + "
-                                        "reduce_kernel")
-                                       if fused else
-                                       ("fwd_kernel (train) + bwds_kernel (fused backward and "
-                                        "weight gradients, in segments) + reduce_kernel")),
+        "roofline_train": {"kernels": {
+                               "one kernel": ("trainw_kernel" if width == 64 else "trainf_kernel") +
+                                             " (the whole step)",
+                               "fused": "fwd_kernel (train) + bwdg_kernel (fused backward and weight "
+                                        "gradients)",
+                               "segments": "fwd_kernel (train) + " +
+                                           ("bwds_kernel" if width >= 64 else "bwdsn_kernel") +
+                                           " (fused backward and weight gradients, in segments)",
+                               "three kernels": "fwd_kernel (train) + bwd_kernel + wgrad_kernel",
+                           }[plan] + " + reduce_kernel",
                            "bound": "hbm", "achieved": train_gbs,
                            "peak": PEAK_HBM_GBS, "unit": "GB/s",
                            "frac": train_gbs / PEAK_HBM_GBS,
-                           "bytes_per_row": train_bytes_per_row(width, depth, in_dim, out_dim,
-                                                                args.act),
+                           "bytes_per_row": step_bytes_per_row(width, depth, in_dim, out_dim,
+                                                               args.act, M),
                            "bytes_per_row_three_kernels": train_bytes_per_row(
                                width, depth, in_dim, out_dim, args.act, fused=False),
                            "bytes_per_row_three_kernels_no_masks": train_bytes_per_row(

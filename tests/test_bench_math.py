@@ -75,6 +75,27 @@ def test_one_kernel_training_bytes_per_row():
         assert not bench.fused_step(w, d)
 
 
+def test_segmented_training_bytes_per_row():
+    """Segments: 4 in + 4 out + 4 d W + 4 OP, the delta between two segments
+    written and read (4 W each), for sine the cos stash written and read."""
+    # 17 matrices of 128 x 128 in 6 segments
+    assert bench.segments(128, 16) == 6
+    assert bench.step_plan(128, 16, 128, 128, "relu", 1 << 19) == "segments"
+    assert bench.step_bytes_per_row(128, 16, 128, 128, "relu", 1 << 19) == \
+        4 * 128 + 4 * 128 + 4 * 16 * 128 + 4 * 128 + 4 * 128 * 5 == 12288
+    # one segment: no delta is stored
+    assert bench.segments(64, 0) == 1
+    assert bench.step_bytes_per_row(64, 0, 40, 12, "relu", 1000) == 4 * 40 + 4 * 12 + 4 * 16
+    assert bench.step_bytes_per_row(16, 8, 16, 16, "sine", 1000) == 4 * 16 + 4 * 16 + 8 * 8 * 16 + 4 * 16
+    # the headline net and the one-kernel steps as before
+    assert bench.step_bytes_per_row(128, 4, 128, 16, "relu", 1 << 20) == 2816
+    assert bench.step_bytes_per_row(64, 4, 64, 16, "relu", 4096) == 2 * 64 + 64
+    # small batches of nets of several segments: the three-kernel count
+    assert bench.step_plan(128, 16, 128, 128, "relu", 50000) == "three kernels"
+    assert bench.step_bytes_per_row(128, 16, 128, 128, "relu", 50000) == \
+        bench.train_bytes_per_row(128, 16, 128, 128, "relu", fused=False)
+
+
 def test_default_steps_paper_protocol():
     """The bench's default step count follows section IV-A's rule,
     max(1000 * 2^18 / M, 250): 250 at 2^20 rows and above, 1000 at 2^18,
