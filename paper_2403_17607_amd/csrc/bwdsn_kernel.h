@@ -104,7 +104,7 @@ __global__ __launch_bounds__(kBwdsWaves * 64) void bwdsn_kernel(const BwdsArgs a
     constexpr int i = decltype(ic)::value;
     const Rows r = rows_of(tile);
     if constexpr (BOT && i == NL - 1) {
-      load_x_strips<W, false, NT, 1>(a.X, r.row0, M, in_dim, li, lg, ab[i]);
+      load_x_strips<W, 1, NT, 1>(a.X, r.row0, M, in_dim, li, lg, ab[i]);
     } else {
       load_img(a.stashA + (size_t)(hi - i - 1) * a.M16 * W, SW, r, ab[i]);
       if constexpr (AC == BWDS_SINE) load_img(a.stashS + (size_t)(hi - i - 1) * a.M16 * W, SW, r, cq[i]);

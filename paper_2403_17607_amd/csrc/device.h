@@ -294,12 +294,34 @@ __device__ __forceinline__ void mask_x_rows(const uint16_t* X, int64_t row0, int
   }
 }
 
+// One load per feature, for rows of few features: an unaligned 16-byte load
+// takes as long as several of these.  0 past in_dim and past M.
+template <int NT, int KBW>
+__device__ __forceinline__ void load_x_features(const uint16_t* X, int64_t row0, int64_t M, int in_dim, int li, int lg,
+                                                u32x4 (&dst)[NT][KBW]) {
+  int64_t vr = M - row0;
+  vr = vr < 0 ? 0 : (vr > NT * 16 ? NT * 16 : vr);
+  const rsrc_t xr = make_rsrc(X + row0 * in_dim, vr * in_dim * 2);
+#pragma unroll
+  for (int kb = 0; kb < KBW; ++kb) {
+    const int f0 = kb * 32 + lg * 8;
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      uint32_t e[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        e[q] = bload16(xr, f0 + q < in_dim ? (uint32_t)((li * in_dim + f0 + q) * 2) : kOOB, (uint32_t)(n * 32 * in_dim));
+      dst[n][kb] = u32x4{e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
+    }
+  }
+}
+
 // The same in strip order: lane (g, i) of block n gets features
 // 16 s + 4 g .. + 3 of row 16 n + i (the order of a tile image's strips), as
 // two strips of one 32-feature operand (k-block kb: strips 2 kb, 2 kb + 1);
-// W = 16 has one strip, the other half is 0.  VEC: in_dim is known to be a
-// multiple of 4.
-template <int W, bool VEC, int NT, int KBW>
+// W = 16 has one strip, the other half is 0.  XU 0: in_dim is known to be a
+// multiple of 4; 1: not known; 2: one load per feature (see load_x_features).
+template <int W, int XU, int NT, int KBW>
 __device__ __forceinline__ void load_x_strips(const uint16_t* X, int64_t row0, int64_t M, int in_dim, int li, int lg,
                                               u32x4 (&dst)[NT][KBW]) {
   auto put = [&](int n, auto sc, u32x2 v) {
@@ -314,7 +336,22 @@ __device__ __forceinline__ void load_x_strips(const uint16_t* X, int64_t row0, i
       dst[n][s >> 1].y = v.y;
     }
   };
-  if (VEC || (in_dim & 3) == 0) {
+  if constexpr (XU == 2) {
+    int64_t vr = M - row0;
+    vr = vr < 0 ? 0 : (vr > NT * 16 ? NT * 16 : vr);
+    const rsrc_t xr = make_rsrc(X + row0 * in_dim, vr * in_dim * 2);
+    static_for<0, W / 16>([&](auto sc) {
+      const int f0 = 16 * decltype(sc)::value + 4 * lg;
+#pragma unroll
+      for (int n = 0; n < NT; ++n) {
+        uint32_t e[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          e[q] = bload16(xr, f0 + q < in_dim ? (uint32_t)((li * in_dim + f0 + q) * 2) : kOOB, (uint32_t)(n * 32 * in_dim));
+        put(n, sc, u32x2{e[0] | (e[1] << 16), e[2] | (e[3] << 16)});
+      }
+    });
+  } else if (XU == 0 || (in_dim & 3) == 0) {
     int64_t vr = M - row0;
     vr = vr < 0 ? 0 : (vr > NT * 16 ? NT * 16 : vr);
     const rsrc_t xr = make_rsrc(X + row0 * in_dim, vr * in_dim * 2);

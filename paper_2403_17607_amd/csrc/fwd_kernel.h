@@ -580,6 +580,16 @@ static FwdPick fwd_pick() {
   return FwdPick{fwd_kernel<W, ACT, MODE, FU, RES, SMALL, LIN, TST, XU>, NW * 64, (int64_t)NW * NT * 16};
 }
 
+// X rows of at most so many features (no multiple of 8) are loaded one feature
+// at a time at widths up to 64 (XU 2): an unaligned 16-byte load takes as long
+// as several 2-byte ones, and needs its rows' ends shifted and cleared.  One
+// load per feature against unaligned loads, inference of 16- and 32-wide nets:
+// in 3, 4096 rows 0.90 of the time, 2^18 rows 0.74-0.87 (2 matrices, out 3 3.7 us
+// against 5.0), 10^6 rows 0.75-0.93; in 11 0.88-1.0 (10^6 rows up to 1.07); in 15
+// 0.94-0.99 up to 2^17 rows, beyond them 1.0-1.3.  Small batches of width 64 and stashing and training
+// forward passes of all three widths: in 3 0.79-0.99, in 15 0.85-1.0.
+constexpr int kFwdFeatures = 12, kFwdFeaturesSmall = 15;
+
 // LIN: the output activation is linear (the common case) and fixed at
 // compile time.  With a runtime output activation the epilogue switches per
 // element, which cost 12% of width-16 inference at 2^20 rows (17.9 -> 15.7
@@ -635,13 +645,17 @@ static hipError_t launch_t(const FwdArgs& a0, hipStream_t stream, int* grid_out)
                : (odd ? fwd_pick<W, ACT, MODE, 4, false, false, LIN, false, XU>()
                       : fwd_pick<W, ACT, MODE, 3, false, false, LIN, false, XU>());
   }
+  if constexpr (MODE == FWD_INFER && W <= 32 && XU == 1) {
+    if (res && a.in_dim <= kFwdFeatures) pk = fwd_pick<W, ACT, MODE, 0, true, false, LIN, false, 2>();
+  }
   if constexpr (W <= 64) {
     // Small batches: fewer than two row tiles of the tile configuration
     // (NT NW 16 rows) per CU (widths up to 64, whose weights leave LDS for
     // several workgroups per CU), inference and training forward alike.
     const int64_t cfg_rows = (int64_t)TileCfg<W>::NT * TileCfg<W>::NW * 16;
     if ((a.M + cfg_rows - 1) / cfg_rows <= 2 * (int64_t)di.cus && res)
-      pk = fwd_pick<W, ACT, MODE, 0, true, true, LIN, false, XU>();
+      pk = a.in_dim <= kFwdFeaturesSmall ? fwd_pick<W, ACT, MODE, 0, true, true, LIN, false, XU == 1 ? 2 : XU>()
+                                         : fwd_pick<W, ACT, MODE, 0, true, true, LIN, false, XU>();
   }
   a.ntiles = (int)((a.M + pk.rows - 1) / pk.rows);
   int occ = 0;

@@ -59,7 +59,7 @@ struct TrainfGeom {
                 "fused training step: widths 16 and 32, 2 .. kTrainfMaxL matrices");
 };
 
-template <int W, int L, int OS, int ACT, bool VEC>
+template <int W, int L, int OS, int ACT, int XU>
 __global__ __launch_bounds__(kTrainfWaves * 64) void trainf_kernel(const TrainfArgs a) {
   using Gm = TrainfGeom<W, L, OS>;
   constexpr int NW = Gm::NW, NT = Gm::NT, SW = Gm::SW, KBW = Gm::KBW;
@@ -120,7 +120,8 @@ __global__ __launch_bounds__(kTrainfWaves * 64) void trainf_kernel(const TrainfA
   // strips (lane (g, i): row i, columns 16 s + 4 g .. + 3).
   u32x4 xin[NT][KBW], tq[NT][OS];
   auto load_x = [&](const Rows& r, u32x4 (&dst)[NT][KBW]) {
-    if constexpr (VEC) load_x_aligned<NT, KBW>(a.X, r.row0, M, in_dim, li, lg, dst);
+    if constexpr (XU == 0) load_x_aligned<NT, KBW>(a.X, r.row0, M, in_dim, li, lg, dst);
+    else if constexpr (XU == 2) load_x_features<NT, KBW>(a.X, r.row0, M, in_dim, li, lg, dst);
     else load_x_unaligned<NT, KBW>(a.X, r.row0, M, in_dim, li, lg, dst);
   };
   auto load_xt = [&](int tile) {
@@ -154,7 +155,7 @@ __global__ __launch_bounds__(kTrainfWaves * 64) void trainf_kernel(const TrainfA
 
     // ---- forward: hidden activations a_1 .. a_{L-1} kept as strips
     // (lane (g, i) of block n: row 16 n + i, features 16 s + 4 g .. + 3).
-    if constexpr (!VEC) mask_x_rows<NT, KBW>(a.X, r.row0, M, in_dim, li, lg, xin);
+    if constexpr (XU == 1) mask_x_rows<NT, KBW>(a.X, r.row0, M, in_dim, li, lg, xin);
     u32x2 st[L - 1][NT][SW];
     u32x2 cs[CSL][NT][SW];  // sine: bf16 cos of the pre-activations
     // k-block kb of layer l's input for block n, chain order
@@ -279,7 +280,7 @@ __global__ __launch_bounds__(kTrainfWaves * 64) void trainf_kernel(const TrainfA
     // conditional one made the wait for the strips before G_0 drain it as
     // well (width 32 at 2^20 rows 54.6 -> 53.0 us).
     u32x4 xs4[NT][KBW];
-    load_x_strips<W, VEC, NT, KBW>(a.X, r.row0, M, in_dim, li, lg, xs4);
+    load_x_strips<W, XU, NT, KBW>(a.X, r.row0, M, in_dim, li, lg, xs4);
     load_xt(tile + G);
 
     // Layer l: G_l += A_l^T D_{l+1} over the wave's rows; for l >= 1 also
@@ -289,7 +290,7 @@ __global__ __launch_bounds__(kTrainfWaves * 64) void trainf_kernel(const TrainfA
       constexpr int l = decltype(lc)::value;
       constexpr int SD = Gm::sd(l), GO = Gm::goff(l);
       if constexpr (l == 0) {
-        if constexpr (!VEC) mask_x_strips<W, NT, KBW>(a.X, r.row0, M, in_dim, li, lg, xs4);
+        if constexpr (XU == 1) mask_x_strips<W, NT, KBW>(a.X, r.row0, M, in_dim, li, lg, xs4);
 #pragma unroll
         for (int n = 0; n < NT; ++n)
 #pragma unroll
@@ -441,7 +442,7 @@ __global__ __launch_bounds__(kTrainfWaves * 64) void trainf_kernel(const TrainfA
   }
 }
 
-template <int W, int L, int OS, int ACT, bool VEC>
+template <int W, int L, int OS, int ACT, int XU>
 static hipError_t trainf_launch_t(const TrainfArgs& a0, hipStream_t stream, int* grid_out) {
   using Gm = TrainfGeom<W, L, OS>;
   TrainfArgs a = a0;
@@ -452,7 +453,7 @@ static hipError_t trainf_launch_t(const TrainfArgs& a0, hipStream_t stream, int*
   if (e != hipSuccess) return e;
   const size_t lds = Gm::lds_bytes();
   if (lds > (size_t)di.max_lds) return hipErrorNotSupported;
-  auto kern = trainf_kernel<W, L, OS, ACT, VEC>;
+  auto kern = trainf_kernel<W, L, OS, ACT, XU>;
   int occ = 0;
   e = kernel_occupancy(reinterpret_cast<const void*>(kern), kTrainfWaves * 64, lds, &occ);
   if (e != hipSuccess) return e;
@@ -465,36 +466,40 @@ static hipError_t trainf_launch_t(const TrainfArgs& a0, hipStream_t stream, int*
   return hipGetLastError();
 }
 
-template <int W, int OS, int ACT, bool VEC>
+template <int W, int OS, int ACT, int XU>
 static hipError_t trainf_by_l(int L, const TrainfArgs& a, hipStream_t s, int* g) {
   switch (L) {
-    case 2: return trainf_launch_t<W, 2, OS, ACT, VEC>(a, s, g);
-    case 3: return trainf_launch_t<W, 3, OS, ACT, VEC>(a, s, g);
-    case 4: return trainf_launch_t<W, 4, OS, ACT, VEC>(a, s, g);
-    case 5: return trainf_launch_t<W, 5, OS, ACT, VEC>(a, s, g);
+    case 2: return trainf_launch_t<W, 2, OS, ACT, XU>(a, s, g);
+    case 3: return trainf_launch_t<W, 3, OS, ACT, XU>(a, s, g);
+    case 4: return trainf_launch_t<W, 4, OS, ACT, XU>(a, s, g);
+    case 5: return trainf_launch_t<W, 5, OS, ACT, XU>(a, s, g);
     default: return hipErrorNotSupported;
   }
 }
 
-// VEC: X rows a multiple of 8 features (aligned 16-byte loads only), the
-// common case, compiled without the unaligned loads of other widths.  Those,
-// one per lane and eight features, took the place of one load per feature:
-// 64-wide, in 37, out 7, 5 matrices, 300000 rows 83.4 -> 61.0 us, in 58, 2
-// sine matrices, 122313 rows 29.4 -> 19.2; 32-wide, in 27, 300000 rows 30.4
-// -> 25.1.
+// XU 0: X rows of whole 16-byte pieces.  1: other widths, one unaligned load per
+// lane and eight features: 32 wide, in 27, 300000 rows 30.4 us with one load per
+// feature, 25.1 with these.  2: rows of few features and one output strip, one
+// load per feature (an unaligned 16-byte load takes as long as several 2-byte
+// ones): against XU 1, in 3, 4096 rows 0.91-0.96 of the time, 10^6 rows 0.77-0.81
+// (16 wide) and 0.67-0.81 (32 wide); 16 wide in 11 0.79-1.05, in 13 up to 1.16; 32
+// wide in 13 0.77-1.0, in 19 up to 1.15.
 template <int W, int OS, int ACT>
-static hipError_t trainf_by_vec(int L, const TrainfArgs& a, hipStream_t s, int* g) {
-  if (a.in_dim % 8 == 0) return trainf_by_l<W, OS, ACT, true>(L, a, s, g);
-  return trainf_by_l<W, OS, ACT, false>(L, a, s, g);
+static hipError_t trainf_by_x(int L, const TrainfArgs& a, hipStream_t s, int* g) {
+  if (a.in_dim % 8 == 0) return trainf_by_l<W, OS, ACT, 0>(L, a, s, g);
+  if constexpr (OS == 1) {
+    if (a.in_dim <= (W == 16 ? 12 : 13)) return trainf_by_l<W, OS, ACT, 2>(L, a, s, g);
+  }
+  return trainf_by_l<W, OS, ACT, 1>(L, a, s, g);
 }
 
 template <int W, int OS>
 static hipError_t trainf_by_act(int act, int L, const TrainfArgs& a, hipStream_t s, int* g) {
   switch (act) {
-    case ACT_RELU: return trainf_by_vec<W, OS, ACT_RELU>(L, a, s, g);
-    case ACT_SIGMOID: return trainf_by_vec<W, OS, ACT_SIGMOID>(L, a, s, g);
-    case ACT_SINE: return trainf_by_vec<W, OS, ACT_SINE>(L, a, s, g);
-    default: return trainf_by_vec<W, OS, ACT_LINEAR>(L, a, s, g);
+    case ACT_RELU: return trainf_by_x<W, OS, ACT_RELU>(L, a, s, g);
+    case ACT_SIGMOID: return trainf_by_x<W, OS, ACT_SIGMOID>(L, a, s, g);
+    case ACT_SINE: return trainf_by_x<W, OS, ACT_SINE>(L, a, s, g);
+    default: return trainf_by_x<W, OS, ACT_LINEAR>(L, a, s, g);
   }
 }
 

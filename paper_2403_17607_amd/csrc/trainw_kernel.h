@@ -540,7 +540,7 @@ static hipError_t trainw_by_l(int L, const TrainfArgs& a, hipStream_t s, int* g)
   }
 }
 
-// VEC: X rows a multiple of 8 features (see trainf_by_vec).
+// VEC: X rows a multiple of 8 features (see trainf_by_x).
 template <int OS, int ACT>
 static hipError_t trainw_by_vec(int L, const TrainfArgs& a, hipStream_t s, int* g) {
   if (a.in_dim % 8 == 0) return trainw_by_l<OS, ACT, true>(L, a, s, g);

@@ -659,6 +659,56 @@ def test_one_kernel_step_shapes(ffmlp, gpu, width, depth, in_dim, out_dim, act, 
     run_case(ffmlp, gpu, width, depth, in_dim, out_dim, M, act, out_act, seed=50 + width + depth)
 
 
+def infer_case(ffmlp, dev, width, depth, in_dim, out_dim, M, act="relu", out_act="linear", seed=61):
+    """Inference at a size where workgroups loop over tiles: bitwise equal to
+    the stashing forward on every row (another kernel, with other tiles), and
+    to the oracle on sampled rows and on the first and last."""
+    log(f"infer w={width} d={depth} in={in_dim} out={out_dim} M={M} act={act} out={out_act}")
+    W = datagen.xavier_weights(seed, width, depth, in_dim, out_dim)
+    Xd = datagen.inputs_uniform(seed, M, in_dim, device=dev)
+    net = ffmlp.FusedMLP(width, depth, in_dim, out_dim, act, out_act)
+    onet = oracle_net(width, depth, in_dim, out_dim, act, out_act)
+    packed = net.pack(W.to(dev))
+    Y = net.forward(packed, Xd)
+    assert torch.equal(net.forward(packed, Xd, stash=net.workspace(M, dev)), Y)
+    rows = torch.unique(torch.cat([sampled_rows(M, 500, seed), torch.arange(min(M, 40)),
+                                   torch.arange(max(0, M - 600), M)])).to(dev)
+    Yref, _ = onet.forward(W, Xd[rows].cpu())
+    log("  output errs", check_outputs(f64(Y[rows]), Yref, onet.L))
+
+
+@pytest.mark.parametrize("width,depth,in_dim,out_dim,M,act,out_act", [
+    (16, 3, 3, 3, 700001, "relu", "linear"), (16, 2, 10, 16, 600007, "sine", "sigmoid"),
+    (16, 4, 11, 5, 600007, "relu", "linear"), (16, 3, 15, 16, 1 << 20, "relu", "linear"),
+    (32, 3, 9, 32, 500003, "relu", "linear"), (32, 1, 11, 7, 400001, "sigmoid", "linear"),
+    (32, 4, 27, 3, 1 << 20, "relu", "sigmoid"), (16, 2, 15, 3, 131072, "relu", "linear"),
+    (32, 2, 15, 3, 131073, "relu", "linear"), (64, 3, 13, 16, 131072, "relu", "linear"),
+    (64, 4, 37, 7, 300001, "relu", "linear"), (64, 3, 63, 16, 300005, "sine", "linear"),
+    (64, 2, 3, 40, 300001, "relu", "linear"), (64, 3, 59, 64, 300003, "relu", "sigmoid"),
+    (64, 20, 33, 3, 300001, "relu", "linear"),
+    (128, 4, 127, 16, 300007, "relu", "linear"), (128, 2, 63, 3, 300007, "relu", "linear"),
+    (128, 3, 127, 108, 300007, "relu", "linear"), (128, 2, 39, 100, 300007, "sine", "linear"),
+    (128, 3, 63, 16, 300007, "relu", "linear"), (128, 6, 63, 4, 300001, "relu", "linear"),
+])
+def test_unaligned_inference_many_tiles(ffmlp, gpu, width, depth, in_dim, out_dim, M, act, out_act):
+    """Input widths that are no multiple of 8, at batch sizes where every
+    workgroup takes several tiles and requests the next tile's X early: odd and
+    even matrix counts, one output strip and several, resident and streamed
+    weights, rows of few features (one load each) and their limits, and the
+    limit of the small-batch tiles."""
+    infer_case(ffmlp, gpu, width, depth, in_dim, out_dim, M, act, out_act)
+
+
+@pytest.mark.parametrize("width,depth,in_dim,out_dim,act,M", [
+    (16, 2, 10, 3, "relu", 200003), (16, 3, 11, 16, "sigmoid", 140001), (16, 1, 1, 16, "sine", 140001),
+    (32, 2, 13, 16, "relu", 140001), (32, 3, 15, 5, "sine", 140001), (32, 4, 3, 20, "relu", 140001),
+])
+def test_few_features_training(ffmlp, gpu, width, depth, in_dim, out_dim, act, M):
+    """The one-kernel step on rows of few features, on both sides of the widths
+    where X is loaded one feature at a time, several tiles per workgroup."""
+    run_case(ffmlp, gpu, width, depth, in_dim, out_dim, M, act, seed=62)
+
+
 def test_argument_errors_on_device(ffmlp, gpu):
     net = ffmlp.FusedMLP(64, 2, 64, 16, "relu")
     W, X, T = inputs(15, 64, 2, 64, 16, 100)
