@@ -59,7 +59,8 @@ struct TrainfGeom {
                 "fused training step: widths 16 and 32, 2 .. kTrainfMaxL matrices");
 };
 
-template <int W, int L, int OS, int ACT, int XU>
+// YV: out_dim is known to be a multiple of 4.
+template <int W, int L, int OS, int ACT, int XU, bool YV>
 __global__ __launch_bounds__(kTrainfWaves * 64) void trainf_kernel(const TrainfArgs a) {
   using Gm = TrainfGeom<W, L, OS>;
   constexpr int NW = Gm::NW, NT = Gm::NT, SW = Gm::SW, KBW = Gm::KBW;
@@ -72,7 +73,7 @@ __global__ __launch_bounds__(kTrainfWaves * 64) void trainf_kernel(const TrainfA
   const int64_t M = a.M;
   const int in_dim = a.in_dim, out_dim = a.out_dim, out_act = a.out_act;
   const int SO = (out_dim + 15) >> 4;
-  const bool yvec = (out_dim & 3) == 0;
+  const bool yvec = YV || (out_dim & 3) == 0;
 
   // Resident weights, both orientations (direct-to-LDS loads).
   stage_frags(smem, a.packedF, a.fwd_total, wave, NW, lane);
@@ -453,7 +454,14 @@ static hipError_t trainf_launch_t(const TrainfArgs& a0, hipStream_t stream, int*
   if (e != hipSuccess) return e;
   const size_t lds = Gm::lds_bytes();
   if (lds > (size_t)di.max_lds) return hipErrorNotSupported;
-  auto kern = trainf_kernel<W, L, OS, ACT, XU>;
+  auto kern = trainf_kernel<W, L, OS, ACT, XU, false>;
+  if constexpr (ACT == ACT_SINE && L == 5 && ((W == 16 && XU == 0) || (W == 32 && OS == 2))) {
+    // With the other output widths' stores in the same kernel, the largest
+    // sine nets spill 6 registers more (32 wide, in 32, out 32, 2^18 rows 5%
+    // slower) or pass 128 registers (16 wide: one workgroup per CU instead of
+    // two, 0.88 of the time at 2^17 rows, 1.04 at 10^6).
+    if (a.out_dim % 4 == 0 && (W == 32 || a.M > (1 << 19))) kern = trainf_kernel<W, L, OS, ACT, XU, true>;
+  }
   int occ = 0;
   e = kernel_occupancy(reinterpret_cast<const void*>(kern), kTrainfWaves * 64, lds, &occ);
   if (e != hipSuccess) return e;
@@ -482,13 +490,13 @@ static hipError_t trainf_by_l(int L, const TrainfArgs& a, hipStream_t s, int* g)
 // feature, 25.1 with these.  2: rows of few features and one output strip, one
 // load per feature (an unaligned 16-byte load takes as long as several 2-byte
 // ones): against XU 1, in 3, 4096 rows 0.91-0.96 of the time, 10^6 rows 0.77-0.81
-// (16 wide) and 0.67-0.81 (32 wide); 16 wide in 11 0.79-1.05, in 13 up to 1.16; 32
+// (16 wide) and 0.67-0.81 (32 wide); 16 wide in 9 0.78-1.0, in 11 0.79-1.05, in 12 up to 1.09; 32
 // wide in 13 0.77-1.0, in 19 up to 1.15.
 template <int W, int OS, int ACT>
 static hipError_t trainf_by_x(int L, const TrainfArgs& a, hipStream_t s, int* g) {
   if (a.in_dim % 8 == 0) return trainf_by_l<W, OS, ACT, 0>(L, a, s, g);
   if constexpr (OS == 1) {
-    if (a.in_dim <= (W == 16 ? 12 : 13)) return trainf_by_l<W, OS, ACT, 2>(L, a, s, g);
+    if (a.in_dim <= (W == 16 ? 10 : 13)) return trainf_by_l<W, OS, ACT, 2>(L, a, s, g);
   }
   return trainf_by_l<W, OS, ACT, 1>(L, a, s, g);
 }

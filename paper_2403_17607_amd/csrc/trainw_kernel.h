@@ -57,7 +57,8 @@ struct TrainwGeom {
                 "width-64 fused training step");
 };
 
-template <int L, int OS, int ACT, bool VEC, int NT>
+// YV: out_dim is known to be a multiple of 4.
+template <int L, int OS, int ACT, bool VEC, int NT, bool YV>
 __global__ __launch_bounds__(kTrainfWaves * 64) void trainw_kernel(const TrainfArgs a) {
   using Gm = TrainwGeom<L, OS, NT>;
   constexpr int NW = Gm::NW, SW = Gm::SW, KBW = Gm::KBW, KBO = Gm::KBO, LDT = Gm::LDT, KS = Gm::KS;
@@ -72,7 +73,7 @@ __global__ __launch_bounds__(kTrainfWaves * 64) void trainw_kernel(const TrainfA
   const int64_t M = a.M;
   const int in_dim = a.in_dim, out_dim = a.out_dim, out_act = a.out_act;
   const int SO = (out_dim + 15) >> 4;
-  const bool yvec = (out_dim & 3) == 0;
+  const bool yvec = YV || (out_dim & 3) == 0;
 
   // Resident weights (direct-to-LDS loads, waited for below).
   stage_frags(smem, a.packedF, a.fwd_total, wave, NW, lane);
@@ -500,7 +501,14 @@ static hipError_t trainw_launch_nt(const TrainfArgs& a0, hipStream_t stream, int
   if (e != hipSuccess) return e;
   const size_t lds = Gm::lds_bytes();
   if (lds > (size_t)di.max_lds) return hipErrorNotSupported;
-  auto kern = trainw_kernel<L, OS, ACT, VEC, NT>;
+  auto kern = trainw_kernel<L, OS, ACT, VEC, NT, false>;
+  if constexpr (L == 2 && OS == 4 && ACT != ACT_SINE && VEC) {
+    // With the other output widths' stores in the same kernel, these pass 128
+    // registers and run one workgroup per CU instead of two: better up to some
+    // four tiles per CU (50000 rows 16.9 us against 19.8, 2^17 rows 22.2 against
+    // 23.0), worse beyond (2^18 rows 34.2 against 32.6, 10^6 rows 118 against 98).
+    if (a.out_dim % 4 == 0 && a.M > (1 << 17)) kern = trainw_kernel<L, OS, ACT, VEC, NT, true>;
+  }
   int occ = 0;
   e = kernel_occupancy(reinterpret_cast<const void*>(kern), kTrainfWaves * 64, lds, &occ);
   if (e != hipSuccess) return e;
