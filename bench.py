@@ -80,7 +80,7 @@ def three_kernels(width, depth, act, rows):
         return n >= 2 and rows <= ((24576 if act == "sine" else 8192) if n == 2 else
                                    (16384 if act == "sigmoid" else 32768))
     if width == 64:
-        return n >= 2 and rows <= (24576 if n == 2 else 49152 if n <= 4 else 40960)
+        return rows <= (24576 if act == "sigmoid" else 40960) if n >= 3 else n == 2 and depth >= 7 and act != "sigmoid" and rows <= 16384
     return act != "sigmoid" and n >= (6 if act == "sine" else 4) and rows <= 16384 * min(n, 8)
 
 

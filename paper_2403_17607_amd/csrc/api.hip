@@ -176,7 +176,7 @@ bool fused_backward(const mlp* h, bool seeded, int64_t M) {
 // relu' from the stashed activations, which they read anyway).
 bool reads_masks(const mlp* h, int64_t M) {
   return h->act == MLP_ACT_RELU && ((h->width == 128 && fused_backward(h, true, M)) ||
-                                    backward_pair(h->width, n_mats(h), h->act, false, M));
+                                    backward_pair(h->width, n_mats(h), h->act, false, false, M));
 }
 
 // Fixed-order sum of P weight-gradient partials (and the loss partials).
@@ -285,7 +285,7 @@ int run_backward(const mlp* h, const void* packed, const uint16_t* X, const floa
                  uint8_t* ws, int64_t M, float* G, float* loss, int nloss, hipStream_t s) {
   if (M <= 0) return run_reduce(h, w, ws, M, 0, G, loss, nloss, s);
   const int L = n_mats(h);
-  if (backward_pair(h->width, L, h->act, dX != nullptr, M))
+  if (backward_pair(h->width, L, h->act, dX != nullptr, dY != nullptr && h->out_act != MLP_ACT_LINEAR, M))
     return run_pair(h, packed, X, dY, dX, w, ws, M, G, loss, nloss, s);
   const PackGeom g = pack_geom(h);
   BwdsPlan p{};

@@ -19,14 +19,16 @@ namespace ffmlp {
 //   128 wide: 1024 rows 91 / 80 us, 32768 rows 1.26, 2^17 rows 0.93
 // Between, over 6 to 33 matrices, the crossing moves with the number of
 // segments and the activation (sigmoid's and sine's delta kernels read a value
-// where ReLU's reads a mask bit; dX adds as much to both): the lines below lie
-// where the two are within some 5%.
-bool backward_pair(int width, int L, int act, bool dx, int64_t M) {
+// where ReLU's reads a mask bit; dX adds as much to both; input widths that are
+// no multiple of 8 cost the pair 5% more; a seeded top with a nonlinear output
+// activation, act_top, costs it up to a quarter more at width 64, 6 to 10
+// matrices): the lines below lie where the two are within some 5%.
+bool backward_pair(int width, int L, int act, bool dx, bool act_top, int64_t M) {
   const int n = bwds_segments(width, L);
   const bool sine = act == ACT_SINE, sigmoid = act == ACT_SIGMOID;
   if (width == 16) return n >= 3 && M <= (sine ? 24576 : (sigmoid ? 4096 : 8192) * (int64_t)(n - 1));
   if (width == 32) return n >= 2 && M <= (n == 2 ? (sine ? 24576 : 8192) : (sigmoid ? 16384 : 32768));
-  if (width == 64) return n >= 2 && M <= (n == 2 ? 24576 : (n <= 4 ? 49152 : 40960));
+  if (width == 64) return n >= 3 ? M <= (act_top ? 16384 : (sigmoid ? 24576 : 40960)) : (n == 2 && L >= 8 && !sigmoid && !act_top && M <= 16384);
   return !sigmoid && n >= (sine ? 6 : (dx ? 5 : 4)) && M <= 16384 * (int64_t)(n < 8 ? n : 8);
 }
 

@@ -36,7 +36,6 @@ __global__ __launch_bounds__(TileCfg<W>::NW * 64) void bwd_kernel(const BwdArgs 
   const int64_t M = a.M;
   const int SO = (out_dim + 15) >> 4;
   const int OP = SO * 16;
-  const bool yvec = (out_dim & 3) == 0;
 
   // Weights: resident in LDS, or staged layer by layer through two LDS
   // buffers with direct-to-LDS loads, the next layer (layer L-1 of the next
@@ -75,55 +74,49 @@ __global__ __launch_bounds__(TileCfg<W>::NW * 64) void bwd_kernel(const BwdArgs 
       const rsrc_t dr = make_rsrc(a.deltaOut + row0 * OP, (int64_t)vblk * 32 * OP);
       const rsrc_t cr = make_rsrc(a.cOut + row0 * OP, a.cOut ? (int64_t)vblk * 64 * OP : 0);
       const rsrc_t gr = make_rsrc(a.dY + row0 * out_dim, a.dY ? vrows * out_dim * 4 : 0);
-      static_for<0, SW>([&](auto sc) {
-        constexpr int s = decltype(sc)::value;
-        if (s >= SO) return;
+      // Seeded: one copy per output activation (a switch per element took 16 us
+      // of 56 in a forward and backward pass of a 64-wide net of 8 matrices, 64
+      // sigmoid outputs, 4223 rows).
+      auto top = [&](auto oac) {
+        constexpr int OA = decltype(oac)::value;
+        static_for<0, SW>([&](auto sc) {
+          constexpr int s = decltype(sc)::value;
+          if (s >= SO) return;
+          // 4-byte aligned; past out_dim the load holds the next row's values
+          const int j0 = s * 16 + lg * 4;
+          const uint32_t eo = j0 < out_dim ? (uint32_t)((li * out_dim + j0) * 4) : kOOB;
 #pragma unroll
-        for (int n = 0; n < NT; ++n) {
-          const uint32_t so = (uint32_t)((n * SO + s) * 512);
-          uint32_t p0, p1;
-          if constexpr (!SEEDED) {
-            const u32x2 v = bload64(dr, lane * 8, so);
-            p0 = v.x;
-            p1 = v.y;
-          } else {
-            const int64_t m = row0 + n * 16 + li;
-            const int j0 = s * 16 + lg * 4;
-            const bool ok = m < M && j0 < out_dim;
-            float g[4] = {0.f, 0.f, 0.f, 0.f};
-            if (yvec) {
-              const uint32_t eo = (j0 < out_dim) ? (uint32_t)(li * out_dim + j0) : kOOB / 4;
-              const u32x4 v = bload128(gr, eo * 4, (uint32_t)(n * 64 * out_dim));
-              g[0] = __uint_as_float(v.x);
-              g[1] = __uint_as_float(v.y);
-              g[2] = __uint_as_float(v.z);
-              g[3] = __uint_as_float(v.w);
-            } else if (ok) {
-              const float* dp = a.dY + m * out_dim + j0;
+          for (int n = 0; n < NT; ++n) {
+            const uint32_t so = (uint32_t)((n * SO + s) * 512);
+            u32x2 p;
+            if constexpr (!SEEDED) {
+              p = bload64(dr, lane * 8, so);
+            } else {
+              const u32x4 v = bload128(gr, eo, (uint32_t)(n * 64 * out_dim));
+              u32x4 cv = {0u, 0u, 0u, 0u};
+              if constexpr (OA != ACT_LINEAR) cv = bload128(cr, lane * 16, (uint32_t)((n * SO + s) * 1024));
+              float g[4];
 #pragma unroll
-              for (int r = 0; r < 4; ++r)
-                if (j0 + r < out_dim) g[r] = dp[r];
+              for (int r = 0; r < 4; ++r) {
+                g[r] = j0 + r < out_dim ? __uint_as_float(v[r]) : 0.f;
+                const float c = __uint_as_float(cv[r]);
+                if constexpr (OA != ACT_LINEAR) g[r] *= act_out_grad(OA, c, act_apply(OA, c));
+              }
+              p = u32x2{pack_bf16x2(g[0], g[1]), pack_bf16x2(g[2], g[3])};
+              bstore64(p, dr, lane * 8, so);
             }
-            if (out_act != ACT_LINEAR) {
-              const u32x4 cv = bload128(cr, lane * 16, (uint32_t)((n * SO + s) * 1024));
-              const float c[4] = {__uint_as_float(cv.x), __uint_as_float(cv.y),
-                                  __uint_as_float(cv.z), __uint_as_float(cv.w)};
-#pragma unroll
-              for (int r = 0; r < 4; ++r) g[r] *= act_out_grad(out_act, c[r], act_apply(out_act, c[r]));
+            if constexpr (s & 1) {
+              dA[n][s >> 1].z = p.x;
+              dA[n][s >> 1].w = p.y;
+            } else {
+              dA[n][s >> 1].x = p.x;
+              dA[n][s >> 1].y = p.y;
             }
-            p0 = pack_bf16x2(g[0], g[1]);
-            p1 = pack_bf16x2(g[2], g[3]);
-            bstore64(u32x2{p0, p1}, dr, lane * 8, so);
           }
-          if (s & 1) {
-            dA[n][s >> 1].z = p0;
-            dA[n][s >> 1].w = p1;
-          } else {
-            dA[n][s >> 1].x = p0;
-            dA[n][s >> 1].y = p1;
-          }
-        }
-      });
+        });
+      };
+      if constexpr (SEEDED) by_act_value(out_act, top);
+      else top(std::integral_constant<int, ACT_LINEAR>{});
     }
 
     // ReLU: the mask words of the activation a layer needs (stash index
@@ -243,7 +236,6 @@ __global__ __launch_bounds__(TileCfg<W>::NW * 64) void bwd_kernel(const BwdArgs 
     auto input_grad = [&](const u32x4 (&in)[NT][KBW]) {
       const int in_dim = a.in_dim;
       const int SI = (in_dim + 15) >> 4;
-      const bool xv = (in_dim & 3) == 0;
       const rsrc_t xr = make_rsrc(a.dX + row0 * in_dim, vrows * in_dim * 4);
       // strip s + 1's fragments are requested while strip s computes
       u32x4 af[KBW], an[KBW];
@@ -266,16 +258,12 @@ __global__ __launch_bounds__(TileCfg<W>::NW * 64) void bwd_kernel(const BwdArgs 
         const int f0 = 16 * s + 4 * lg;
 #pragma unroll
         for (int n = 0; n < NT; ++n) {
-          if (xv) {
-            const uint32_t eo = f0 < in_dim ? (uint32_t)((li * in_dim + f0) * 4) : kOOB;
-            bstore128(__builtin_bit_cast(u32x4, acc[n]), xr, eo, (uint32_t)(n * 16 * in_dim * 4));
+          const uint32_t eo = (uint32_t)((li * in_dim + f0) * 4), so = (uint32_t)(n * 64 * in_dim);
+          if ((in_dim & 3) == 0 || f0 + 4 <= in_dim) {
+            bstore128(__builtin_bit_cast(u32x4, acc[n]), xr, f0 < in_dim ? eo : kOOB, so);
           } else {
-            const int64_t m = row0 + n * 16 + li;
-            if (m < M) {
 #pragma unroll
-              for (int r = 0; r < 4; ++r)
-                if (f0 + r < in_dim) a.dX[m * in_dim + f0 + r] = acc[n][r];
-            }
+            for (int q = 0; q < 4; ++q) bstore32(__float_as_uint(acc[n][q]), xr, f0 + q < in_dim ? eo + 4 * q : kOOB, so);
           }
         }
       }

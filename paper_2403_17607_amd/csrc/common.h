@@ -257,8 +257,9 @@ hipError_t launch_forward(int width, int act, int mode, const FwdArgs& a,
                           hipStream_t s, int* grid_out);
 hipError_t launch_backward(int width, int act, int seeded, const BwdArgs& a, hipStream_t s);
 hipError_t launch_wgrad(int width, const WgradArgs& a, hipStream_t s);
-// Whether a batch of M rows runs these two (dx: with the input gradient).
-bool backward_pair(int width, int L, int act, bool dx, int64_t M);
+// Whether a batch of M rows runs these two (dx: with the input gradient;
+// act_top: seeded, with a nonlinear output activation; both only make it rarer).
+bool backward_pair(int width, int L, int act, bool dx, bool act_top, int64_t M);
 // Fused backward pass and weight-gradient partials; *grid_out receives the
 // number of partials written.
 hipError_t launch_backward_fused(int width, int L, int out_dim, int seeded, const BwdgArgs& a, hipStream_t s,

@@ -108,6 +108,15 @@ __device__ __forceinline__ void train_epilogue(const f32x4& acc, const u32x4& t,
   d = u32x2{pack_bf16x2(dv[0], dv[1]), pack_bf16x2(dv[2], dv[3])};
 }
 
+// f(std::integral_constant<int, act>{}) for a run-time activation.
+template <typename F>
+__device__ __forceinline__ void by_act_value(int act, F&& f) {
+  if (act == ACT_LINEAR) f(std::integral_constant<int, ACT_LINEAR>{});
+  else if (act == ACT_RELU) f(std::integral_constant<int, ACT_RELU>{});
+  else if (act == ACT_SIGMOID) f(std::integral_constant<int, ACT_SIGMOID>{});
+  else f(std::integral_constant<int, ACT_SINE>{});
+}
+
 // Derivative of a hidden activation from what the forward pass stored: the
 // bf16 activation a (ReLU: a > 0, sigmoid: a (1 - a)) or, for sine, the
 // stored bf16 cos(c) passed in as a.

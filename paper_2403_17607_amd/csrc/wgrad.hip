@@ -114,10 +114,19 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const WgradArgs a) {
   auto load_chunk = [&](int64_t c) {
     const int64_t c0 = c * CH;
     const __amdgpu_buffer_rsrc_t rd_src = rsrc(dsrc, c0, dF * 2, a.M16);
-    const __amdgpu_buffer_rsrc_t ra_src =
-        xmode ? rsrc(a.X, c0, in_dim * 2, xvec ? M : 0) : rsrc(asrc, c0, W * 2, a.M16);
+    if (xmode && !xvec) {
+      const XPieces<8> x(a.X, c0, M, in_dim, CH);
 #pragma unroll
-    for (int k = 0; k < UPT; ++k) ra[k] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(ra_src, voa[k], 0, kLoadPol));
+      for (int k = 0; k < UPT; ++k) {
+        const int q = (k >> 1) * 256 + tid;
+        if (q < (CH / 2) * nf8)
+          ra[k] = x_piece_load<8, u32x4, u32x4_a2>(x, 2 * (q % (CH / 2)) + (k & 1), (q / (CH / 2)) * 8, in_dim);
+      }
+    } else {
+      const __amdgpu_buffer_rsrc_t ra_src = xmode ? rsrc(a.X, c0, in_dim * 2, M) : rsrc(asrc, c0, W * 2, a.M16);
+#pragma unroll
+      for (int k = 0; k < UPT; ++k) ra[k] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(ra_src, voa[k], 0, kLoadPol));
+    }
 #pragma unroll
     for (int k = 0; k < UPT; ++k) rd[k] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rd_src, vod[k], 0, kLoadPol));
   };
@@ -158,13 +167,17 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const WgradArgs a) {
       }
     }
   };
-  // Other input widths: X goes straight from global memory into LDS,
-  // element by element, when the chunk is stored (no register staging).
-  auto copy_x_scalar = [&](int64_t c0) {
-    for (int u = tid; u < CH * in_dim; u += 256) {
-      const int ml = u / in_dim, f = u - ml * in_dim;
-      const int64_t row = c0 + ml;
-      AT[(size_t)f * LDT + ml] = row < M ? a.X[row * in_dim + f] : (uint16_t)0;
+  // Other input widths: unaligned 16-byte loads (device.h), a load that would
+  // pass the end of X shifted into place and rows past M cleared here, then as
+  // above.  One load per element took longer than all the rest of the kernel
+  // (64 wide, 9 matrices, in 63, 4096 rows: training step 40.7 -> 31.9 us).
+  auto fix_x = [&](int64_t c0) {
+    const XPieces<8> x(a.X, c0, M, in_dim, CH);
+    const bool tail = !x.tiny && (x.rows < CH || x.rem < (CH - 1) * in_dim + ((in_dim - 1) & ~7));
+#pragma unroll
+    for (int k = 0; k < UPT; ++k) {
+      const int q = (k >> 1) * 256 + tid;
+      if (q < (CH / 2) * nf8) x_piece_fix<8>(x, 2 * (q % (CH / 2)) + (k & 1), (q / (CH / 2)) * 8, in_dim, tail, ra[k]);
     }
   };
 
@@ -183,8 +196,10 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const WgradArgs a) {
   for (int64_t c = c_begin; c < c_end; ++c) {
     __syncthreads();  // every wave is done reading the previous chunk
     if (!xmode) store_tile(ra, AT32, W);
-    else if (xvec) store_x(ra);
-    else copy_x_scalar(c * CH);
+    else {
+      if (!xvec) fix_x(c * CH);
+      store_x(ra);
+    }
     store_tile(rd, DT32, dF);
     __syncthreads();
     if (c + 1 < c_end) load_chunk(c + 1);
