@@ -177,7 +177,7 @@ int mlp_backward_dx(const mlp_t* h, const void* packed, const uint16_t* X,
  * stores every delta and one that contracts them.
  * Then a fixed-order reduction, so G and the loss are bitwise the same from
  * run to run.  mlp_backward runs that fused kernel under the same rule, and
- * at width 64 with 2 to 5 matrices and in_dim a multiple of 8 up to some 10^5
+ * at width 64 with 2 to 5 matrices and in_dim a multiple of 4 up to some 10^5
  * rows; otherwise, as mlp_backward_dx does for every net, the segments or
  * (small batches) the two kernels.
  */

@@ -7,18 +7,19 @@ namespace ffmlp {
 
 // Without the input gradient, 2 to 5 matrices.  Width 128: ReLU nets with one
 // output strip (register budget).  Width 64: seeded passes with X rows of whole
-// 16-byte pieces.  There the segments (bwds_kernel.h) have some 2 us more before
+// 8-byte pieces.  There the segments (bwds_kernel.h) have some 2 us more before
 // their first tile, and this kernel more registers from 3 matrices on (one
 // workgroup per CU), so the segments take large batches.  Backward and reduce,
 // segments against this kernel (us): ReLU, out 3: 2 matrices 1024 rows 8.2 /
 // 6.7, 10^6 rows 64 / 60; 3 matrices 1024 rows 9.7 / 8.6, 2^17 rows 23.2 / 22.4,
 // 2^18 rows 32 / 35; 5 matrices 1024 rows 12.8 / 10.9, 2^17 rows 34.3 / 33.7; sine: 3
-// matrices 1024 rows 10.1 / 8.9, 2^16 rows 18.3 / 17.1, 10^5 rows equal.  Other
-// input widths gain less than 5% at 1024 rows and lose from 40000 on.
+// matrices 1024 rows 10.1 / 8.9, 2^16 rows 18.3 / 17.1, 10^5 rows equal.  Input
+// widths that are no multiple of 4 gain less than 5% at 1024 rows and lose from
+// 40000 on.
 bool backward_fused_supported(int width, int L, int act, int in_dim, int out_dim, bool seeded, int64_t M) {
   if (L < 2 || L > kBwdgMaxL) return false;
   if (width == 128) return act == ACT_RELU && out_dim <= 16;
-  if (width != 64 || !seeded || in_dim % 8 != 0) return false;
+  if (width != 64 || !seeded || in_dim % 4 != 0) return false;
   if (L == 2) return true;
   return M <= (act == ACT_RELU ? 1 << 17 : 1 << 16);
 }

@@ -558,8 +558,7 @@ static hipError_t bwdg_launch_t(const BwdgArgs& a, hipStream_t stream, int* grid
     return hipErrorInvalidValue;
   }
   if (a.in_dim % 8 == 0) return bwdg_launch_t1<W, L, OS, SEEDED, DER, true>(a, stream, grid_out);
-  if constexpr (W == 128) return bwdg_launch_t1<W, L, OS, SEEDED, DER, false>(a, stream, grid_out);
-  return hipErrorInvalidValue;  // width 64: multiples of 8 only
+  return bwdg_launch_t1<W, L, OS, SEEDED, DER, false>(a, stream, grid_out);
 }
 
 template <int W, int OS, int SEEDED, int DER>
