@@ -267,8 +267,10 @@ __global__ __launch_bounds__((fwd_waves<W, MODE, SMALL, FU, XU>() * 64)) void fw
       const size_t soff = (size_t)l * a.M16 * W + (size_t)row0 * W;
       const rsrc_t sa = make_rsrc(a.stashA + soff, a.stashA ? (int64_t)vblk * 32 * W : 0);
       const rsrc_t ss = make_rsrc(a.stashS + soff, a.stashS ? (int64_t)vblk * 32 * W : 0);
-      // ReLU mask words of this layer's activation (training, ReLU nets)
-      constexpr bool MASK = MODE != FWD_INFER && ACT == ACT_RELU;
+      // ReLU mask words of this layer's activation, where a backward kernel
+      // reads them: with the transposed stash always, and then made strip by
+      // strip beside the MFMAs; otherwise from the layer's whole output below.
+      constexpr bool MASK = TST && ACT == ACT_RELU;
       uint32_t mk[NT];
 #pragma unroll
       for (int n = 0; n < NT; ++n) mk[n] = 0u;
@@ -337,11 +339,22 @@ __global__ __launch_bounds__((fwd_waves<W, MODE, SMALL, FU, XU>() * 64)) void fw
         // Keep each strip's work together: bounds the live registers.
         __builtin_amdgcn_sched_barrier(0);
       });
-      if constexpr (MASK) {
-        const rsrc_t mr = make_rsrc(a.reluMask + ((size_t)l * (a.M16 / 16) + tb0) * 64,
-                                    a.reluMask ? (int64_t)vblk * 256 : 0);
+      if constexpr (MODE != FWD_INFER && ACT == ACT_RELU) {
+        if (MASK || a.reluMask != nullptr) {
+          if constexpr (!MASK) {
+            static_for<0, SW>([&](auto sc) {
+              constexpr int s = decltype(sc)::value;
 #pragma unroll
-        for (int n = 0; n < NT; ++n) bstore32<NTS>(mk[n], mr, lane * 4, (uint32_t)(n * 256));
+              for (int n = 0; n < NT; ++n) {
+                const u32x4 o = out[n][s >> 1];
+                mk[n] |= (nonzero_halves((s & 1) ? o.z : o.x) | (nonzero_halves((s & 1) ? o.w : o.y) << 1)) << (2 * s);
+              }
+            });
+          }
+          const rsrc_t mr = make_rsrc(a.reluMask + ((size_t)l * (a.M16 / 16) + tb0) * 64, (int64_t)vblk * 256);
+#pragma unroll
+          for (int n = 0; n < NT; ++n) bstore32<NTS>(mk[n], mr, lane * 4, (uint32_t)(n * 256));
+        }
       }
       if (!resident) {
         drain_and_sync();  // next layer staged; this buffer free again
