@@ -598,10 +598,10 @@ static FwdPick fwd_pick() {
 // as several 2-byte ones, and needs its rows' ends shifted and cleared.  One
 // load per feature against unaligned loads, inference of 16- and 32-wide nets:
 // in 3, 4096 rows 0.90 of the time, 2^18 rows 0.74-0.87 (2 matrices, out 3 3.7 us
-// against 5.0), 10^6 rows 0.75-0.93; in 11 0.88-1.0 (10^6 rows up to 1.07); in 15
+// against 5.0), 10^6 rows 0.75-0.93; in 9 0.85-1.0 (one matrix, in 12 up to 1.19); in 15
 // 0.94-0.99 up to 2^17 rows, beyond them 1.0-1.3.  Small batches of width 64 and stashing and training
 // forward passes of all three widths: in 3 0.79-0.99, in 15 0.85-1.0.
-constexpr int kFwdFeatures = 12, kFwdFeaturesSmall = 15;
+constexpr int kFwdFeatures = 10, kFwdFeaturesSmall = 15;
 
 // LIN: the output activation is linear (the common case) and fixed at
 // compile time.  With a runtime output activation the epilogue switches per
@@ -624,8 +624,10 @@ static hipError_t launch_t(const FwdArgs& a0, hipStream_t stream, int* grid_out)
   a.resident = res_bytes + (MODE == FWD_INFER ? 0 : 1024) <= (size_t)di.max_lds ? 1 : 0;
   const size_t lds = a.resident ? res_bytes : (size_t)2 * maxf * 1024;
   const bool res = a.resident != 0, odd = (a.L & 1) != 0;
-  FwdPick pk = res ? fwd_pick<W, ACT, MODE, 0, true, false, LIN, false, XU>()
-                   : fwd_pick<W, ACT, MODE, 0, false, false, LIN, false, XU>();
+  FwdPick pk = fwd_pick<W, ACT, MODE, 0, true, false, LIN, false, XU>();
+  if constexpr (MODE != FWD_INFER || W <= 32) {  // wider inference picks below
+    if (!res) pk = fwd_pick<W, ACT, MODE, 0, false, false, LIN, false, XU>();
+  }
   if constexpr (W == 128 && MODE == FWD_TRAIN) {
     if (a.stash_t)
       pk = res ? fwd_pick<W, ACT, MODE, 0, true, false, LIN, true, XU>()
@@ -635,16 +637,24 @@ static hipError_t launch_t(const FwdArgs& a0, hipStream_t stream, int* grid_out)
   }
   if constexpr (MODE == FWD_INFER && W == 128 && XU == 1) {
     // The unaligned loads need more registers than 16 waves leave.  Where 12
-    // waves cost more than they bring (streamed weights are staged once per
-    // tile of 384 instead of 512 rows: 7 matrices, in 63, 300001 rows 69 against
-    // 64 us; the even-matrix fused loop: 4 matrices, in 63, 2^20 rows 95 against
-    // 90), X is loaded one feature at a time.  Resident weights otherwise: in
-    // 39, out 108, 4 matrices, 284203 rows 42.2 -> 33.3 us; in 127, 5 matrices,
+    // waves cost more than they bring, X is loaded one feature at a time:
+    // streamed weights (staged once per tile of 384 instead of 512 rows: 7
+    // matrices, in 63, 300001 rows 69 against 64 us), the even-matrix fused loop
+    // (4 matrices, in 63, 2^20 rows 95 against 90), and batches of few rounds of
+    // tiles where 384-row tiles take more of them (2 matrices, out 100, in 63:
+    // 110000 rows, two rounds against one, 1.33 times the time; 200000 rows, three
+    // against two, 1.13; 280000, three each, 0.82; one matrix is bound by X alone
+    // and loses).  Resident weights otherwise:
+    // in 39, out 108, 4 matrices, 284203 rows 42.2 -> 33.3 us; in 127, 5 matrices,
     // 2^20 rows 158.7 -> 147.2.
-    if (!res) pk = fwd_pick<W, ACT, MODE, 0, false, false, LIN, false, 2>();
+    const int64_t r12 = (a.M + 384 * (int64_t)di.cus - 1) / (384 * (int64_t)di.cus);
+    const int64_t r16 = (a.M + 512 * (int64_t)di.cus - 1) / (512 * (int64_t)di.cus);
+    if (!res)
+      pk = fwd_pick<W, ACT, MODE, 0, false, false, LIN, false, 2>();
+    else if (a.L >= 2 && ((r16 <= 4 && 3 * r12 > 4 * r16) || (SO == 1 && !odd)))
+      pk = fwd_pick<W, ACT, MODE, 0, true, false, LIN, false, 2>();
     else if (a.L >= 2 && SO == 1)
-      pk = odd ? fwd_pick<W, ACT, MODE, 1, true, false, LIN, false, XU>()
-               : fwd_pick<W, ACT, MODE, 0, true, false, LIN, false, 2>();
+      pk = fwd_pick<W, ACT, MODE, 1, true, false, LIN, false, XU>();
     else if (a.L >= 2)
       pk = odd ? fwd_pick<W, ACT, MODE, 4, true, false, LIN, false, XU>()
                : fwd_pick<W, ACT, MODE, 3, true, false, LIN, false, XU>();
