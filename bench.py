@@ -77,10 +77,14 @@ def three_kernels(width, depth, act, rows):
     if width == 16:
         return n >= 3 and rows <= {"sine": 24576, "sigmoid": 4096 * (n - 1)}.get(act, 8192 * (n - 1))
     if width == 32:
-        return n >= 2 and rows <= ((24576 if act == "sine" else 8192) if n == 2 else
-                                   (16384 if act == "sigmoid" else 32768))
+        if n == 1:
+            return depth == 6 and act == "sine" and rows <= 16384
+        return rows <= ((24576 if act == "sine" else 8192) if n == 2 else
+                        (16384 if act == "sigmoid" else 32768))
     if width == 64:
-        return rows <= (24576 if act == "sigmoid" else 40960) if n >= 3 else n == 2 and depth >= 7 and act != "sigmoid" and rows <= 16384
+        if n >= 3:
+            return rows <= (24576 if act == "sigmoid" else 40960)
+        return n == 2 and depth >= 7 and act != "sigmoid" and rows <= 16384
     return act != "sigmoid" and n >= (6 if act == "sine" else 4) and rows <= 16384 * min(n, 8)
 
 

@@ -418,8 +418,17 @@ static hipError_t bwds_by_pos(const BwdsArgs& a, hipStream_t s) {
   return hipErrorNotSupported;
 }
 
-// Longest segment, and the shortest of a net of several: with n segments of
-// at most bwds_max layers for more than (n - 1) bwds_max, each has at least
+// Longest segment.  Width 128: three layers' weights (96 KiB) and the two row
+// tiles (64 KiB) are all of LDS.  Width 64: five layers' G and operands take the
+// 128 registers that let two workgroups share a CU.  Width 32: seven layers' G
+// alone is 112 registers per lane.  Width 16: nine layers' kernels take 108 to
+// 165.  The sine kernels of the longest segments hold a second source value per
+// element and spill (width 32, 7 matrices, up to 64 registers; width 64, 5
+// matrices, 12); from some 20000 rows on they are faster all the same than the
+// delta and gradient kernels (32 wide, 7 sine matrices, 50000 rows 0.98 of their
+// time, 2^17 rows 0.7-0.9), below that backward_pair takes those.
+// The shortest segment of a net of several: with n segments of at most
+// bwds_max layers for more than (n - 1) bwds_max, each has at least
 // (bwds_max + 1) / 2.
 constexpr int bwds_max(int width) { return width == 128 ? 3 : (width == 64 ? 5 : (width == 32 ? 7 : 9)); }
 

@@ -296,6 +296,7 @@ def test_segmented_backward(ffmlp, gpu, width, depth, in64, out64, M, act, out_a
 
 @pytest.mark.parametrize("width,depth,in_dim,out_dim,M,act", [
     (16, 18, 16, 16, 16384, "relu"), (16, 18, 13, 3, 24577, "sine"),
+    (32, 6, 31, 5, 16384, "sine"), (32, 6, 31, 5, 16385, "sine"),
     (32, 7, 32, 5, 8192, "relu"), (32, 7, 32, 5, 8193, "relu"), (32, 14, 31, 32, 16384, "sigmoid"),
     (32, 14, 31, 32, 16385, "sigmoid"), (32, 8, 9, 17, 24576, "sine"), (32, 8, 9, 17, 24577, "sine"),
     (64, 7, 63, 3, 16384, "relu"), (64, 7, 63, 3, 16385, "relu"), (64, 9, 3, 64, 16384, "sine"), (64, 10, 40, 64, 40961, "sine"),
@@ -304,7 +305,8 @@ def test_segmented_backward(ffmlp, gpu, width, depth, in64, out64, M, act, out_a
     (128, 15, 128, 1, 3001, "sine"),
 ])
 def test_small_batches_of_deep_nets(ffmlp, gpu, width, depth, in_dim, out_dim, M, act):
-    """Nets of several segments up to the batch size where the delta and
+    """Nets of several segments (and of one that spills, 32 wide, 7 sine
+    matrices) up to the batch size where the delta and
     gradient kernels run instead, and just past it: seeded with and without
     dX, and the training step, the last bitwise the same on a second call.
     (16 wide, 19 matrices, in 13 runs as a sine net: with these ReLU inputs a
