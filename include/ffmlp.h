@@ -18,8 +18,9 @@
  * width x width, width x out_dim (for depth = 0: one in_dim x out_dim
  * matrix).  width is 16, 32, 64 or 128 (section I); 1 <= in_dim, out_dim
  * <= width; 0 <= depth <= MLP_MAX_DEPTH (the weight-gradient launch has one
- * grid row per matrix, and a grid dimension holds at most 65535).  Smaller input and output widths are reduced to the square case
- * by zero padding inside the library (section III-A).
+ * grid row per matrix, and a grid dimension holds at most 65535).  Smaller
+ * input and output widths are reduced to the square case by zero padding
+ * inside the library (section III-A).
  *
  * Precision.  All matrix products take bf16 operands and accumulate in fp32
  * (section III-B).  Every activation, delta and output stored is rounded

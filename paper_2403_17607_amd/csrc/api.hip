@@ -91,6 +91,11 @@ WsLayout ws_layout(const mlp* h, int64_t M) {
   const int OP = strips(h->out_dim) * 16;
   w.M16 = (M + 15) / 16 * 16;
   const size_t hid = (size_t)(L - 1) * w.M16 * W * 2;
+  // Sizes never fall as M grows, so a workspace of some batch serves all smaller
+  // ones.  That is why they are those of the largest user whatever M: deltaH
+  // holds every hidden delta (the delta and gradient kernels of small batches;
+  // the segments only use those between them), reluMask every ReLU net's masks,
+  // partial the gradient kernel's split.
   size_t o = 0;
   w.stashA = o; o = round_up(o + hid, 256);
   w.stashS = o; o = round_up(o + (h->act == MLP_ACT_SINE ? hid : 0), 256);
@@ -289,7 +294,7 @@ int run_backward(const mlp* h, const void* packed, const uint16_t* X, const floa
     return run_pair(h, packed, X, dY, dX, w, ws, M, G, loss, nloss, s);
   const PackGeom g = pack_geom(h);
   BwdsPlan p{};
-  hipError_t e = bwds_plan(h->width, L, h->act, M, &p);
+  hipError_t e = bwds_plan(h->width, L, M, &p);
   if (e != hipSuccess) return hip_fail(e, "backward plan");
   BwdsArgs b{};
   const uint8_t* pk = static_cast<const uint8_t*>(packed);

@@ -8,8 +8,7 @@ namespace ffmlp {
 
 int bwds_segments(int width, int L) { return (L + bwds_max(width) - 1) / bwds_max(width); }
 
-hipError_t bwds_plan(int width, int L, int act, int64_t M, BwdsPlan* out) {
-  (void)act;
+hipError_t bwds_plan(int width, int L, int64_t M, BwdsPlan* out) {
   DeviceInfo di;
   hipError_t e = device_info(&di);
   if (e != hipSuccess) return e;

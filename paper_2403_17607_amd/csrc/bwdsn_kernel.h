@@ -3,8 +3,8 @@
 // 16x16 tiles, so every wave keeps the segment's G in registers and contracts
 // over its own two 16-row blocks only.  No LDS tile and no barrier in the
 // tile loop; LDS holds the segment's weights, and at the end the waves' G is
-// added through it in a fixed order.  The inputs of the next three layers (of this
-// tile or the next) are in flight while a layer computes.
+// added through it in a fixed order.  The inputs of the next three layers (of
+// this tile or the next) are in flight while a layer computes.
 #pragma once
 
 #include "bwds_kernel.h"
@@ -52,7 +52,8 @@ __global__ __launch_bounds__(kBwdsWaves * 64) void bwdsn_kernel(const BwdsArgs a
       stage_frags(smem + (size_t)i * LF * 64, a.packed + (size_t)(hi - i - 1) * LF * 64, (uint32_t)LF, wave, NW, lane);
     }
   });
-  // Selection matrices (see bwds_kernel.h): transpose strip 0 / 1 of an operand.
+  // Selection matrices: an MFMA of an operand whose lane (g, i) holds row i
+  // with one of these 0/1 matrices transposes its strip 0 or 1 exactly.
   u32x4 sel0 = {0u, 0u, 0u, 0u}, sel1 = {0u, 0u, 0u, 0u};
   {
     const int q = li - 4 * lg;

@@ -168,9 +168,9 @@ struct BwdgArgs {
   int stash_t;               // stashA written transposed (FwdArgs::stash_t)
 };
 
-// Fused training step (trainf_kernel): the forward pass, the loss, the
-// backward pass and the weight gradients of nets of width 16 and 32 in one
-// kernel; the hidden activations stay in registers.
+// Fused training step (trainf_kernel at widths 16 and 32, trainw_kernel at
+// width 64): the forward pass, the loss, the backward pass and the weight
+// gradients in one kernel; the hidden activations stay in registers.
 constexpr int kTrainfWaves = 8;  // waves per workgroup
 constexpr int kTrainfMaxL = 5;   // weight matrices of the largest net
 struct TrainfArgs {
@@ -278,7 +278,7 @@ bool train_fused_supported(int width, int L);
 hipError_t launch_bwds(int width, const BwdsArgs& a, hipStream_t s);
 // Number of segments of a net of L matrices.
 int bwds_segments(int width, int L);
-hipError_t bwds_plan(int width, int L, int act, int64_t M, BwdsPlan* out);
+hipError_t bwds_plan(int width, int L, int64_t M, BwdsPlan* out);
 hipError_t launch_reduce(const ReduceArgs& a, hipStream_t s);
 hipError_t launch_pack(const PackArgs& a, hipStream_t s);
 hipError_t launch_optim(const OptArgs& a, hipStream_t s);

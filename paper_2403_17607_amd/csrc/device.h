@@ -409,9 +409,10 @@ __device__ __forceinline__ void mask_x_strips(const uint16_t* X, int64_t row0, i
 // Position 8 c + e of a row holds, for activations and deltas (chain order),
 // feature chain_feature(8 c + e); for X (input order) feature 8 c + e.
 // A 16-value piece q of row r is stored at piece q ^ (r mod pieces) with its
-// two chunks swapped where the next bit of r is set: the 16-byte stores of
-// one chunk in 8 (16) rows and the reads of one piece in 4 rows per lane
-// group then touch distinct banks.
+// two chunks swapped where the next bit of r is set, so that the 16-byte stores
+// of one chunk in 8 (16) rows and the reads of one piece in 4 rows per lane group
+// spread over the banks.  Counted over the segmented kernels that use it, bank
+// conflicts still take 6-7% of the active cycles at width 128 and 15% at 64.
 template <int W>
 struct RowTile {
   static constexpr int RB = W * 2, NQ = W / 16;  // bytes per row, pieces

@@ -597,10 +597,11 @@ static FwdPick fwd_pick() {
 // at a time at widths up to 64 (XU 2): an unaligned 16-byte load takes as long
 // as several 2-byte ones, and needs its rows' ends shifted and cleared.  One
 // load per feature against unaligned loads, inference of 16- and 32-wide nets:
-// in 3, 4096 rows 0.90 of the time, 2^18 rows 0.74-0.87 (2 matrices, out 3 3.7 us
-// against 5.0), 10^6 rows 0.75-0.93; in 9 0.85-1.0 (one matrix, in 12 up to 1.19); in 15
-// 0.94-0.99 up to 2^17 rows, beyond them 1.0-1.3.  Small batches of width 64 and stashing and training
-// forward passes of all three widths: in 3 0.79-0.99, in 15 0.85-1.0.
+// in 3, 4096 rows 0.90 of the time, 2^18 rows 0.74-0.87 (2 matrices, out 3 3.7
+// us against 5.0), 10^6 rows 0.75-0.93; in 9 0.85-1.0 (one matrix, in 12 up to
+// 1.19); in 15 0.94-0.99 up to 2^17 rows, beyond them 1.0-1.3.  Small batches of
+// width 64 and stashing and training forward passes of all three widths: in 3
+// 0.79-0.99, in 15 0.85-1.0.
 constexpr int kFwdFeatures = 10, kFwdFeaturesSmall = 15;
 
 // LIN: the output activation is linear (the common case) and fixed at
@@ -707,7 +708,10 @@ static hipError_t by_mode(int mode, const FwdArgs& a, hipStream_t s, int* g) {
 }
 // XU: X rows that are not whole 16-byte pieces are loaded unaligned.  Its own
 // kernel: both kinds of load in one held registers that width-128 inference
-// does not have.
+// does not have.  The width-128 stashing and training forward kernels spill 2 to
+// 31 registers with it and are still faster than with one load per feature, over
+// 2 to 9 matrices and 4096 to 2^20 rows: 0.56-1.0 of its time, in 127, 5 10^5
+// rows (stash) 1.06.
 template <int W, int ACT>
 static hipError_t by_x(int mode, const FwdArgs& a, hipStream_t s, int* g) {
   return (a.in_dim & 7) == 0 ? by_mode<W, ACT, 0>(mode, a, s, g) : by_mode<W, ACT, 1>(mode, a, s, g);

@@ -87,8 +87,8 @@ def test_depths(ffmlp, gpu, width, depth):
 
 def _random_shapes(n, seed=2024):
     """Seeded shapes across the launch variants: every width, depths 0-6,
-    in/out widths that are and are not multiples of 8 (vector or scalar X
-    and Y paths), every activation pair, ragged batches."""
+    in/out widths that are and are not multiples of 8 (aligned or other
+    X loads and Y stores), every activation pair, ragged batches."""
     import random
     rng = random.Random(seed)
     acts = ["linear", "relu", "sigmoid", "sine"]
@@ -316,6 +316,29 @@ def test_small_batches_of_deep_nets(ffmlp, gpu, width, depth, in_dim, out_dim, M
     r = run_case(ffmlp, gpu, width, depth, in_dim, out_dim, M, act, seed=34)
     G, loss = r["net"].train_step(r["packed"], r["X"].to(gpu), r["T"].to(gpu), r["ws"])
     assert torch.equal(G, r["G"]) and torch.equal(loss, r["loss"])
+
+
+@pytest.mark.parametrize("width,depth,in_dim,out_dim,M,act,out_act", [
+    (16, 9, 13, 3, 150001, "sigmoid", "linear"), (16, 18, 16, 16, 150001, "sine", "sigmoid"),
+    (32, 7, 31, 20, 140003, "sine", "linear"), (32, 14, 8, 32, 140003, "linear", "sigmoid"),
+    (64, 5, 63, 17, 150001, "sine", "linear"), (64, 9, 40, 64, 100003, "sigmoid", "relu"),
+    (128, 3, 127, 16, 70001, "sine", "linear"), (128, 5, 35, 100, 70001, "sigmoid", "linear"),
+    (128, 6, 128, 3, 100003, "linear", "sine"),
+])
+def test_segments_of_many_tiles(ffmlp, gpu, width, depth, in_dim, out_dim, M, act, out_act):
+    """Several segments, each workgroup of them looping over several tiles
+    with the next tile's activations, deltas and X already in flight: every
+    width, aligned and unaligned X, seeded with and without dX and from the
+    training forward; G bitwise the same on a second call."""
+    dx_case(ffmlp, gpu, width, depth, in_dim, out_dim, M, act, out_act, seed=35)
+    r = run_case(ffmlp, gpu, width, depth, in_dim, out_dim, M, act, out_act, seed=36)
+    net, packed, X = r["net"], r["packed"], r["X"].to(gpu)
+    G, loss = net.train_step(packed, X, r["T"].to(gpu), r["ws"])
+    assert torch.equal(G, r["G"]) and torch.equal(loss, r["loss"])
+    dY = datagen.uniform(36, datagen.STREAM_AUX, (M, out_dim)).to(gpu)
+    net.forward(packed, X, stash=r["ws"])
+    G = net.backward(packed, X, dY, r["ws"])
+    assert torch.equal(net.backward(packed, X, dY, r["ws"]), G)
 
 
 def test_input_gradient_streaming(ffmlp, gpu):
@@ -596,13 +619,14 @@ def test_train_step_full_batch(ffmlp, gpu, width, depth, in_dim, out_dim, M):
     (16, 3, 7, 16, "sine", "sine"), (16, 1, 16, 16, "linear", "relu"),
 ])
 def test_fused_backward_shapes(ffmlp, gpu, width, depth, in_dim, out_dim, act, out_act):
-    """Nets of 2 to 5 matrices take the fused backward kernel (deltas kept
-    on chip, weight gradients in registers): every width, both output-strip
-    classes at width 64, input widths that are multiples of 4 and ones that
-    are not (7, 30), every hidden activation at the narrow widths, every
-    output activation, and a batch of several tiles per workgroup with a
-    ragged tail.  The training step and the seeded backward (after a
-    stashing forward) against the oracle."""
+    """Backward passes of nets of 2 to 5 matrices, deltas kept on chip and
+    weight gradients in registers: bwdg_kernel (width 128 ReLU with one output
+    strip; width 64 seeded) or one or two segments, the one-kernel step at
+    widths up to 64; input widths that are multiples of 4 and ones that are
+    not (7, 30), every hidden activation at the narrow widths, every output
+    activation, and a batch of several tiles per workgroup with a ragged tail.
+    The training step and the seeded backward (after a stashing forward)
+    against the oracle."""
     M = 70001
     log(f"fused w={width} d={depth} in={in_dim} out={out_dim} act={act} out_act={out_act} M={M}")
     r = run_case(ffmlp, gpu, width, depth, in_dim, out_dim, M, act, out_act, seed=40 + depth)
@@ -624,8 +648,8 @@ def test_fused_backward_shapes(ffmlp, gpu, width, depth, in_dim, out_dim, act, o
     (64, 16, "sine", "linear", 65537), (16, 3, "relu", "linear", 131072), (16, 3, "relu", "linear", 131073),
     (4, 3, "relu", "linear", 70003), (60, 50, "sine", "sigmoid", 9001), (36, 16, "sigmoid", "linear", 7)])
 def test_seeded_width_64(ffmlp, gpu, depth, in_dim, out_dim, act, out_act, M):
-    """Seeded passes of 2 to 5 matrices at width 64 and X rows of a
-    multiple of 4 run the fused kernel (bwdg_kernel): every derivative source, one output
+    """Seeded passes of 2 to 5 matrices at width 64 and X rows of a multiple
+    of 4 run the fused kernel (bwdg_kernel): every derivative source, one output
     strip and several, one row, ragged tiles and several per workgroup, and the
     two sides of the batch size where the segments take over; G against the
     segments' (backward_dx) and the oracle's, and bitwise the same again."""
@@ -655,11 +679,13 @@ def test_seeded_width_64(ffmlp, gpu, depth, in_dim, out_dim, act, out_act, M):
 ])
 def test_one_kernel_step_shapes(ffmlp, gpu, width, depth, in_dim, out_dim, act, out_act, M):
     """The one-kernel training step (widths 16, 32, 64 with 2 to 5 matrices)
-    across its variants: vector and per-element X, T and Y paths (in_dim a
-    multiple of 8 or not, out_dim a multiple of 4 or not), one and several
-    output strips, every hidden and output activation, a single row, ragged
-    tiles and several tiles per workgroup.  Y (bitwise equal to inference),
-    G and the loss against the oracle."""
+    across its variants: aligned, unaligned and per-feature X loads (in_dim a
+    multiple of 8 or not, and small), Y stored whole or per element (out_dim
+    a multiple of 4 or not), one and several output strips, every hidden and
+    output activation, a single row, ragged tiles, several tiles per workgroup
+    and both sides of the 24576 rows up to which 64-wide nets take one block
+    per wave.  Y (bitwise equal to inference), G and the loss against the
+    oracle."""
     run_case(ffmlp, gpu, width, depth, in_dim, out_dim, M, act, out_act, seed=50 + width + depth)
 
 
