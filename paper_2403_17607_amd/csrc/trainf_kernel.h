@@ -490,8 +490,8 @@ static hipError_t trainf_by_l(int L, const TrainfArgs& a, hipStream_t s, int* g)
 // feature, 25.1 with these.  2: rows of few features and one output strip, one
 // load per feature (an unaligned 16-byte load takes as long as several 2-byte
 // ones): against XU 1, in 3, 4096 rows 0.91-0.96 of the time, 10^6 rows 0.77-0.81
-// (16 wide) and 0.67-0.81 (32 wide); 16 wide in 9 0.78-1.0, in 11 0.79-1.05, in 12 up to 1.09; 32
-// wide in 13 0.77-1.0, in 19 up to 1.15.
+// (16 wide) and 0.67-0.81 (32 wide); 16 wide in 9 0.78-1.0, in 11 0.79-1.05, in
+// 12 up to 1.09; 32 wide in 13 0.77-1.0, in 19 up to 1.15.
 template <int W, int OS, int ACT>
 static hipError_t trainf_by_x(int L, const TrainfArgs& a, hipStream_t s, int* g) {
   if (a.in_dim % 8 == 0) return trainf_by_l<W, OS, ACT, 0>(L, a, s, g);
