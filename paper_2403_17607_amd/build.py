@@ -18,11 +18,14 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libffmlp.so")
-SOURCES = ["api.hip", "fwd.hip", "fwd16.hip", "fwd32.hip", "fwd64.hip", "fwd128.hip", 
-           "bwdg.hip", "bwdg64.hip", "bwdg128.hip",
+SOURCES = ["api.hip", "fwd.hip", "fwd16.hip", "fwd32.hip", "fwd64.hip", "fwd64u.hip",
+           "fwd128.hip", "fwd128u.hip", "bwdg.hip", "bwdg64.hip", "bwdg128.hip",
            "bwd.hip", "bwd16.hip", "bwd32.hip", "bwd64.hip", "bwd128.hip", "wgrad.hip",
            "bwds.hip", "bwds16.hip", "bwds32.hip", "bwds64.hip", "bwds128.hip",
            "trainf.hip", "trainf16.hip", "trainf32.hip", "trainf64.hip", "reduce.hip", "optim.hip"]
+# The longest compilations, started first so that none runs on alone at the end.
+SLOW = ["trainf64.hip", "fwd64u.hip", "fwd128u.hip", "fwd64.hip", "fwd128.hip", "trainf32.hip", "fwd32.hip", "fwd16.hip",
+        "bwds128.hip"]
 ARCH = "gfx950"
 
 HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
@@ -67,7 +70,8 @@ def build(verbose: bool = False, incremental: bool = False) -> str:
     every header are not recompiled."""
     os.makedirs(BUILD, exist_ok=True)
     with ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 1, 16)) as ex:
-        objs = list(ex.map(lambda src: _compile(src, incremental), SOURCES))
+        jobs = {src: ex.submit(_compile, src, incremental) for src in SLOW + [s for s in SOURCES if s not in SLOW]}
+        objs = [jobs[src].result() for src in SOURCES]
     tmp = LIB + f".tmp{os.getpid()}"
     cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", tmp]
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -4,8 +4,13 @@
 namespace ffmlp {
 
 template <>
-hipError_t launch_forward_w<16>(int act, int mode, const FwdArgs& a, hipStream_t s, int* grid_out) {
-  return by_act<16>(act, mode, a, s, grid_out);
+hipError_t launch_forward_w<16, 0>(int act, int mode, const FwdArgs& a, hipStream_t s, int* grid_out) {
+  return by_act<16, 0>(act, mode, a, s, grid_out);
+}
+
+template <>
+hipError_t launch_forward_w<16, 1>(int act, int mode, const FwdArgs& a, hipStream_t s, int* grid_out) {
+  return by_act<16, 1>(act, mode, a, s, grid_out);
 }
 
 }  // namespace ffmlp

@@ -4,8 +4,13 @@
 namespace ffmlp {
 
 template <>
-hipError_t launch_forward_w<32>(int act, int mode, const FwdArgs& a, hipStream_t s, int* grid_out) {
-  return by_act<32>(act, mode, a, s, grid_out);
+hipError_t launch_forward_w<32, 0>(int act, int mode, const FwdArgs& a, hipStream_t s, int* grid_out) {
+  return by_act<32, 0>(act, mode, a, s, grid_out);
+}
+
+template <>
+hipError_t launch_forward_w<32, 1>(int act, int mode, const FwdArgs& a, hipStream_t s, int* grid_out) {
+  return by_act<32, 1>(act, mode, a, s, grid_out);
 }
 
 }  // namespace ffmlp

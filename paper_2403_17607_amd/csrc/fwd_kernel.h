@@ -712,25 +712,20 @@ static hipError_t by_mode(int mode, const FwdArgs& a, hipStream_t s, int* g) {
 // 31 registers with it and are still faster than with one load per feature, over
 // 2 to 9 matrices and 4096 to 2^20 rows: 0.56-1.0 of its time, in 127, 5 10^5
 // rows (stash) 1.06.
-template <int W, int ACT>
-static hipError_t by_x(int mode, const FwdArgs& a, hipStream_t s, int* g) {
-  return (a.in_dim & 7) == 0 ? by_mode<W, ACT, 0>(mode, a, s, g) : by_mode<W, ACT, 1>(mode, a, s, g);
-}
-
-template <int W>
+template <int W, int XU>
 static hipError_t by_act(int act, int mode, const FwdArgs& a, hipStream_t s, int* g) {
   switch (act) {
-    case ACT_RELU: return by_x<W, ACT_RELU>(mode, a, s, g);
-    case ACT_SIGMOID: return by_x<W, ACT_SIGMOID>(mode, a, s, g);
-    case ACT_SINE: return by_x<W, ACT_SINE>(mode, a, s, g);
-    default: return by_x<W, ACT_LINEAR>(mode, a, s, g);
+    case ACT_RELU: return by_mode<W, ACT_RELU, XU>(mode, a, s, g);
+    case ACT_SIGMOID: return by_mode<W, ACT_SIGMOID, XU>(mode, a, s, g);
+    case ACT_SINE: return by_mode<W, ACT_SINE, XU>(mode, a, s, g);
+    default: return by_mode<W, ACT_LINEAR, XU>(mode, a, s, g);
   }
 }
 
-// Per-width entry points, each compiled in its own translation unit
-// (fwd16.hip .. fwd128.hip) so the build runs in parallel; fwd.hip
-// dispatches on the width.
-template <int W>
+// Entry points per width, for X rows of whole 16-byte pieces (XU 0) and others
+// (XU 1), compiled in translation units of their own (fwd16.hip .. fwd128u.hip)
+// so the build runs in parallel; fwd.hip dispatches.
+template <int W, int XU>
 hipError_t launch_forward_w(int act, int mode, const FwdArgs& a, hipStream_t s, int* grid_out);
 
 }  // namespace ffmlp
