@@ -15,11 +15,14 @@ namespace ffmlp {
 // 2^18 rows 32 / 35; 5 matrices 1024 rows 12.8 / 10.9, 2^17 rows 34.3 / 33.7; sine: 3
 // matrices 1024 rows 10.1 / 8.9, 2^16 rows 18.3 / 17.1, 10^5 rows equal.  Input
 // widths that are no multiple of 4 gain less than 5% at 1024 rows and lose from
-// 40000 on.
+// 40000 on.  dY of several strips that are not whole is loaded by element, which
+// costs large batches more than they gain (2 matrices, out 26, 65536 rows 1.09 of
+// the segments' time, 10^6 rows 1.2-1.3).
 bool backward_fused_supported(int width, int L, int act, int in_dim, int out_dim, bool seeded, int64_t M) {
   if (L < 2 || L > kBwdgMaxL) return false;
   if (width == 128) return act == ACT_RELU && out_dim <= 16;
   if (width != 64 || !seeded || in_dim % 4 != 0) return false;
+  if (out_dim > 16 && out_dim % 4 != 0 && M > 1 << 15) return false;
   if (L == 2) return true;
   return M <= (act == ACT_RELU ? 1 << 17 : 1 << 16);
 }

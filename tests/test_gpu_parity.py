@@ -646,7 +646,8 @@ def test_fused_backward_shapes(ffmlp, gpu, width, depth, in_dim, out_dim, act, o
     (8, 1, "relu", "sine", 1), (64, 64, "relu", "linear", 33000), (40, 17, "sine", "linear", 129),
     (64, 16, "sigmoid", "relu", 34001), (24, 33, "linear", "sigmoid", 4000), (64, 16, "sine", "linear", 65536),
     (64, 16, "sine", "linear", 65537), (16, 3, "relu", "linear", 131072), (16, 3, "relu", "linear", 131073),
-    (4, 3, "relu", "linear", 70003), (60, 50, "sine", "sigmoid", 9001), (36, 16, "sigmoid", "linear", 7)])
+    (4, 3, "relu", "linear", 70003), (60, 50, "sine", "sigmoid", 9001), (36, 16, "sigmoid", "linear", 7),
+    (40, 26, "relu", "linear", 32768), (40, 26, "relu", "linear", 32769)])
 def test_seeded_width_64(ffmlp, gpu, depth, in_dim, out_dim, act, out_act, M):
     """Seeded passes of 2 to 5 matrices at width 64 and X rows of a multiple
     of 4 run the fused kernel (bwdg_kernel): every derivative source, one output
