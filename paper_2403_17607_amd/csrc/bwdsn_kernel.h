@@ -26,8 +26,18 @@ struct BwdsnGeom {
   static_assert(W <= 32, "narrow segmented backward");
 };
 
+// The seeded kernel of whole 16-wide sine nets of 4 matrices takes 133 registers
+// by itself and is held to the 128 that let two workgroups share a CU: 500000
+// rows 0.81-0.92 of the time.  (The 6-layer top segment, 132 registers, spills 2
+// and loses up to 5%.)
 template <int W, int NL, bool TOP, bool BOT, bool SEEDED, int AC>
-__global__ __launch_bounds__(kBwdsWaves * 64) void bwdsn_kernel(const BwdsArgs a) {
+constexpr int bwdsn_min_waves() {
+  return W == 16 && AC == BWDS_SINE && NL == 4 && TOP && BOT && SEEDED ? 4 : 2;
+}
+
+template <int W, int NL, bool TOP, bool BOT, bool SEEDED, int AC>
+__global__ __launch_bounds__(kBwdsWaves * 64, (bwdsn_min_waves<W, NL, TOP, BOT, SEEDED, AC>()))
+void bwdsn_kernel(const BwdsArgs a) {
   using Gm = BwdsnGeom<W, NL>;
   constexpr int NW = Gm::NW, NT = Gm::NT, SW = Gm::SW, LF = Gm::LF, TPW = Gm::TPW;
   static_assert(TOP || !SEEDED, "dY enters at the output layer");
