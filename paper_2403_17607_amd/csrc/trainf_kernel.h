@@ -59,9 +59,11 @@ struct TrainfGeom {
                 "fused training step: widths 16 and 32, 2 .. kTrainfMaxL matrices");
 };
 
-// YV: out_dim is known to be a multiple of 4.
+// YV: out_dim is known to be a multiple of 4.  The 3-matrix sine kernel with
+// unaligned X takes 129 registers by itself and is held to the 128 that let two
+// workgroups share a CU (10^6 rows 0.81 of the time).
 template <int W, int L, int OS, int ACT, int XU, bool YV>
-__global__ __launch_bounds__(kTrainfWaves * 64) void trainf_kernel(const TrainfArgs a) {
+__global__ __launch_bounds__(kTrainfWaves * 64, (W == 16 && L == 3 && ACT == ACT_SINE && XU == 1 ? 4 : 2)) void trainf_kernel(const TrainfArgs a) {
   using Gm = TrainfGeom<W, L, OS>;
   constexpr int NW = Gm::NW, NT = Gm::NT, SW = Gm::SW, KBW = Gm::KBW;
   constexpr int NACC = Gm::nacc();
@@ -466,6 +468,11 @@ static hipError_t trainf_launch_t(const TrainfArgs& a0, hipStream_t stream, int*
   e = kernel_occupancy(reinterpret_cast<const void*>(kern), kTrainfWaves * 64, lds, &occ);
   if (e != hipSuccess) return e;
   int grid = di.cus * occ;
+  // Width 16, two workgroups per CU: with up to two tiles per CU one workgroup
+  // takes both, since each fills its own weights and writes its own partial G
+  // (5 ReLU matrices, in 16, out 3, 121347 rows 13.3 -> 10.8 us; 2 matrices 0.79
+  // of the time; 66000 rows, where the second tile would be a tail, up to 1.05).
+  if (W == 16 && a.ntiles <= 2 * di.cus && 8 * a.ntiles > 9 * di.cus && grid > di.cus) grid = di.cus;
   if (grid > a.ntiles) grid = a.ntiles;
   if (grid > kBwdgMaxBlocks) grid = kBwdgMaxBlocks;
   if (grid < 1) grid = 1;

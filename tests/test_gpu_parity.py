@@ -677,6 +677,8 @@ def test_seeded_width_64(ffmlp, gpu, depth, in_dim, out_dim, act, out_act, M):
     (64, 4, 63, 3, "relu", "linear", 24576), (64, 4, 63, 3, "relu", "linear", 24577),
     (64, 3, 37, 7, "sigmoid", "sigmoid", 70001), (64, 1, 64, 16, "relu", "linear", 24577),
     (64, 4, 37, 7, "relu", "linear", 131077),
+    (16, 4, 16, 3, "relu", "linear", 73728), (16, 4, 16, 3, "relu", "linear", 73985),
+    (16, 1, 8, 16, "sigmoid", "linear", 131072), (16, 2, 13, 5, "sine", "linear", 131073),
 ])
 def test_one_kernel_step_shapes(ffmlp, gpu, width, depth, in_dim, out_dim, act, out_act, M):
     """The one-kernel training step (widths 16, 32, 64 with 2 to 5 matrices)
