@@ -69,6 +69,16 @@ constexpr int fwd_waves() {
   if constexpr (W == 128 && MODE == FWD_INFER && !SMALL) return (FU == 2 || XU == 1) ? 12 : 16;
   return (SMALL || (W <= 32 && MODE == FWD_INFER)) ? 8 : TileCfg<W>::NW;
 }
+// Waves per SIMD that the registers must allow: as many as a workgroup needs,
+// and 3 where the unaligned X of 64-wide inference with streamed weights would
+// leave 2 (171 registers; 21 matrices, out 3, 140000-719586 rows 0.83-0.95 of the
+// time with 4 spilled, sine 0.90-1.04).  With resident weights the 12 spilled
+// registers cost more where LDS holds two workgroups (9 matrices 1.01-1.14).
+template <int W, int MODE, bool RES, bool SMALL, int FU, int XU>
+constexpr int fwd_min_waves() {
+  if constexpr (W == 64 && MODE == FWD_INFER && FU == 4 && XU == 1 && !RES) return 3;
+  return (fwd_waves<W, MODE, SMALL, FU, XU>() + 3) / 4;
+}
 // 16-row blocks per wave.
 template <int W, int MODE, bool SMALL = false, int FU = 0>
 constexpr int fwd_nt() {
@@ -87,7 +97,8 @@ constexpr int fwd_nt() {
 // spare.  Same bytes, same addresses.
 template <int W, int ACT, int MODE, int FU, bool RES, bool SMALL = false, bool LIN = false, bool TST = false,
           int XU = 0>
-__global__ __launch_bounds__((fwd_waves<W, MODE, SMALL, FU, XU>() * 64)) void fwd_kernel(const FwdArgs a) {
+__global__ __launch_bounds__((fwd_waves<W, MODE, SMALL, FU, XU>() * 64), (fwd_min_waves<W, MODE, RES, SMALL, FU, XU>()))
+void fwd_kernel(const FwdArgs a) {
   constexpr int NT = fwd_nt<W, MODE, SMALL, FU>(), NW = fwd_waves<W, MODE, SMALL, FU, XU>();
   constexpr int KBW = (W + 31) / 32, SW = W / 16;
   extern __shared__ u32x4 smem[];
@@ -668,9 +679,21 @@ static hipError_t launch_t(const FwdArgs& a0, hipStream_t stream, int* grid_out)
                       : fwd_pick<W, ACT, MODE, 3, true, false, LIN, false, XU>())
                : (odd ? fwd_pick<W, ACT, MODE, 4, false, false, LIN, false, XU>()
                       : fwd_pick<W, ACT, MODE, 3, false, false, LIN, false, XU>());
+    if constexpr (W == 64 && XU == 1) {
+      // The odd-matrix loop takes 180 registers with unaligned loads, 2 waves per
+      // SIMD; one load per feature takes 151, 3 waves, where LDS holds as many
+      // workgroups of 4 waves (3 and 5 matrices, in 1 and 5, 140000-719586 rows
+      // 0.84-1.03 of the time; in 15 up to 1.12; 9 matrices, two workgroups, up to
+      // 1.10).
+      if (res && odd && a.L >= 2 && SO > 1 && a.in_dim <= kFwdFeatures && 3 * lds <= (size_t)di.max_lds)
+        pk = fwd_pick<W, ACT, MODE, 4, true, false, LIN, false, 2>();
+    }
   }
   if constexpr (MODE == FWD_INFER && W <= 32 && XU == 1) {
-    if (res && a.in_dim <= kFwdFeatures) pk = fwd_pick<W, ACT, MODE, 0, true, false, LIN, false, 2>();
+    // One matrix: in 9 0.85 of the time, in 10 up to 1.24; with two output strips
+    // in 6 up to 1.18.
+    if (res && a.in_dim <= (a.L >= 2 ? kFwdFeatures : (SO == 1 ? 9 : 3)))
+      pk = fwd_pick<W, ACT, MODE, 0, true, false, LIN, false, 2>();
   }
   if constexpr (W <= 64) {
     // Small batches: fewer than two row tiles of the tile configuration

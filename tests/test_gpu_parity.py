@@ -719,6 +719,10 @@ def infer_case(ffmlp, dev, width, depth, in_dim, out_dim, M, act="relu", out_act
     (64, 4, 37, 7, 300001, "relu", "linear"), (64, 3, 63, 16, 300005, "sine", "linear"),
     (64, 2, 3, 40, 300001, "relu", "linear"), (64, 3, 59, 64, 300003, "relu", "sigmoid"),
     (64, 20, 33, 3, 300001, "relu", "linear"),
+    (64, 4, 10, 40, 300001, "relu", "linear"), (64, 2, 1, 64, 300001, "sine", "sigmoid"),
+    (64, 6, 9, 23, 300001, "relu", "linear"),
+    (16, 0, 9, 16, 400001, "relu", "linear"), (32, 0, 3, 32, 400001, "sine", "linear"),
+    (32, 0, 5, 32, 400001, "sigmoid", "linear"),
     (128, 4, 127, 16, 300007, "relu", "linear"), (128, 2, 63, 3, 300007, "relu", "linear"),
     (128, 3, 127, 108, 300007, "relu", "linear"), (128, 2, 39, 100, 300007, "sine", "linear"),
     (128, 3, 63, 16, 300007, "relu", "linear"), (128, 6, 63, 4, 300001, "relu", "linear"),
